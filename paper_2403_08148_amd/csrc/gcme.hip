@@ -1,7 +1,7 @@
 // Host side of the GCMe engine: C ABI, validation, device buffers, mesh and
 // cell plans, per-type-pair tables, hipGraph-captured steps and the
 // autotuner.  All arithmetic of the method runs in the kernels of cells.hip,
-// pair.hip, pme.hip and integrate.hip.
+// pair_kernels.h, pme.hip and integrate.hip.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -539,6 +539,7 @@ gcme_status build_plan(gcme_handle h) {
       d.nc[k] = nc;
       double hcell = p.box[k] / nc;
       d.hf[k] = (float)hcell;
+      d.ihf[k] = 1.0f / d.hf[k];
       int reach = (int)std::ceil(p.rc / hcell - 1e-9);
       d.reach[k] = (2 * reach + 1 > nc) ? -1 : reach;
       d.nreach[k] = std::max(1, reach);
@@ -548,6 +549,10 @@ gcme_status build_plan(gcme_handle h) {
     d.rc = p.rc;
     d.rc2 = p.rc * p.rc;
     d.rc2f = (float)d.rc2;
+    // the float list test with rclf never drops a pair that the pair kernels'
+    // own test (in their precision) keeps
+    d.rclf = (float)(p.rc * (1.0 + 1e-5));
+    d.rclmf = d.rclf + 1e-4f * std::max(d.hf[0], std::max(d.hf[1], d.hf[2]));
     d.beta = p.beta;
     d.betaf = (float)p.beta;
     d.lB = p.lB;

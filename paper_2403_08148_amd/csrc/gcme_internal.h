@@ -18,6 +18,25 @@ constexpr int YX_SMALL_THREADS = 256;  // the same for planes up to 48 x 48
 constexpr int FSHIFT_MIXED = 32;
 constexpr int FSHIFT_FP64 = 40;
 
+// A copy of the plan entry *p (a work item or a replica's constants: memory
+// that no kernel writes), read by scalar loads through the constant address
+// space: every field that is used sits in scalar registers.  Plain loads of
+// them turn into one vector load per lane wherever a store may come before
+// them, and all that is computed from them into vector code.  p must be the
+// same for the whole wavefront.
+template <typename T>
+__device__ inline T uniform_load(const T* p) {
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  typedef const __attribute__((address_space(4))) uint32_t* cptr;
+  cptr q = (cptr)(uintptr_t)__builtin_assume_aligned(p, alignof(T));
+  uint32_t w[sizeof(T) / 4];
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(T) / 4; ++i) w[i] = q[i];
+  T r;
+  __builtin_memcpy(&r, w, sizeof(T));
+  return r;
+}
+
 // Per-replica geometry and method constants (device resident).
 struct RepDesc {
   double L[3];
@@ -29,6 +48,9 @@ struct RepDesc {
   float rc2f;
   float betaf, lBf;
   float hf[3];        // cell edge
+  float ihf[3];       // its inverse
+  float rclf;         // list cutoff: rc and a hair
+  float rclmf;        // enumeration radius: rclf plus a margin of the cell edge
   int nc[3];          // cells per axis
   int reach[3];       // stencil half-width in cells; -1 = take the whole axis
   int nreach[3];      // ceil(rc / cell edge): neighbourhood half-width of a brick
@@ -237,11 +259,12 @@ __device__ inline void bin_bead(const CellView& c, const RepDesc& R, uint32_t ux
 __device__ inline int xcd_item(int b, int n) {
   constexpr int X = 8;
   const int per = n / X, rem = n % X, x = b % X;
-  return x * per + (x < rem ? x : rem) + b / X;
+  return __builtin_amdgcn_readfirstlane(x * per + (x < rem ? x : rem) + b / X);
 }
 
 __device__ inline void wave_stamp(unsigned long long* st, int end) {
-  if (st && (threadIdx.x & 63) == 0) {
+  if (!st) return;  // (on its own, so that what follows stays wave-uniform)
+  if ((threadIdx.x & 63) == 0) {
     const unsigned w = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     st[2 * (size_t)w + end] = wall_clock64();
   }

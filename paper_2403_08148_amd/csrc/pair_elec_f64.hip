@@ -1,0 +1,6 @@
+// Real-space electrostatics of the charged pairs in double precision.
+#include "pair_dispatch.h"
+
+namespace gcme {
+template void dispatch_ci<double, true>(hipStream_t s, const PairLaunch& a, bool ev, bool adj, bool count);
+}  // namespace gcme

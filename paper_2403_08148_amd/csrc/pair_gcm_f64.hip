@@ -1,0 +1,6 @@
+// Excluded-volume pairs in double precision.
+#include "pair_dispatch.h"
+
+namespace gcme {
+template void dispatch_ci<double, false>(hipStream_t s, const PairLaunch& a, bool ev, bool adj, bool count);
+}  // namespace gcme
