@@ -331,7 +331,7 @@ gcme_status gcme_forces_energy_noalloc(const gcme_params* p, int32_t n_beads, in
  * its cell columns directly).  Both visit the same pairs with the same
  * cutoff test; they differ in the order of the per-bead sums. */
 typedef struct {
-    int32_t cells_per_cutoff;    /* cell edge ~ rc / n (1..4) */
+    int32_t cells_per_cutoff;    /* cells of about (rc / n)^3, flat along z (1..4) */
     int32_t beads_per_cluster;   /* excluded-volume cluster size (2, 4, 8) */
     int32_t charges_per_cluster; /* real-space electrostatics cluster size (2, 4, 8) */
     int32_t list_slack_pct;      /* list capacity above the density estimate, % (0..1000) */

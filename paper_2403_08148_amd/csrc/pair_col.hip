@@ -106,7 +106,7 @@ __device__ __attribute__((always_inline)) inline void static_for(F&& f) {
 // A cluster bead as the half-shell kernels read it.
 template <typename T>
 struct IBead {
-  T x, y, z;  // relative to bead 0
+  T x, y, z;  // relative to the centre
   int trow;   // type x MAXT: its row of the pair tables
   T q;        // charge number
 };
@@ -119,9 +119,9 @@ struct IBead {
 // consecutive beads at a time, one per lane; a bead within the list cutoff
 // of the cluster's bounding box joins a 128-entry LDS ring of pending
 // candidates, and every 64 pending candidates are evaluated at once, a lane
-// per candidate against every cluster bead.  In the cluster's frame (bead 0's;
+// per candidate against every cluster bead.  In the cluster's frame (the centre's;
 // every column cluster in bulk) the ring holds the candidate's position
-// relative to bead 0, so a pair costs a subtraction per axis; otherwise the
+// relative to the centre, so a pair costs a subtraction per axis; otherwise the
 // fixed-point record, and each pair takes its own minimum image.
 //
 // HALF false: every column within reach (both ends of each pair; no
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(NL_WAVES * 64) void k_pair_col(PairLaunch a) {
       cexpb = -R.beta * R.beta * 1.4426950408889634;
       tsb = 1.1283791670955126 * R.beta;
     }
-    // the cluster beads, wave-uniform: positions relative to bead 0, the
+    // the cluster beads, wave-uniform: positions relative to the centre, the
     // type row of the pair tables and the charge (slots beyond ni: far from
     // everything, so the unrolled pairs need no branch; the general path
     // masks them)
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(NL_WAVES * 64) void k_pair_col(PairLaunch a) {
     int head = 0, tail = 0;  // wave-uniform: candidates evaluated / appended
     // n <= 64 pending candidates from head, one per lane (head is a multiple
     // of 64 here: every drain but the last takes exactly 64).  FRAME: ring
-    // positions relative to bead 0; MASK: the drain holds cluster beads,
+    // positions relative to the centre; MASK: the drain holds cluster beads,
     // whose pairs with the cluster count only for k < j - first.
     auto drain = [&](int n) __attribute__((always_inline)) {
       const int q = (head & 64) + lane;
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(NL_WAVES * 64) void k_pair_col(PairLaunch a) {
         eval(TT{}, FF{});
       head += n;
     };
-    // the list cutoff around the cluster's bounding box (relative to bead 0)
+    // the list cutoff around the cluster's bounding box (relative to the centre)
     const float rcl2 = K.rcl * K.rcl;
     int* cand = s_cand[wave];
     // the candidates cand[0, total), 64 per chunk (one per lane): those within

@@ -155,16 +155,22 @@ __device__ inline long long to_fixed(double f, double scale, unsigned int* statu
 // Candidate enumeration, shared by the list build and the list-free kernel
 // ---------------------------------------------------------------------------
 
-// A cluster's geometry as wave-uniform values, in float relative to the
-// lower corner of bead 0's cell: every value is a few cells at most, so float
-// carries it to ~1e-7 of a cell, and the margin in rclm keeps each cell range
-// conservative.
+// A cluster's geometry as wave-uniform values.  Positions are taken relative
+// to the centre of the bounding box of its beads: the frame's floats are then
+// as small as they can be, and with them the rounding of the separation of
+// close pairs, and each is rounded once, from double (forces of the adsorption
+// study's slab, whose electrode beads are stiff: 2.5e-7 off; 3.6e-7 with the
+// conversion in single precision, 5.2e-7 with bead 0 for the origin; 1% of
+// the kernel's time).  Cell ranges are in float relative to
+// the lower corner of the centre's cell: every value is a few cells at most,
+// so float carries it to ~1e-7 of a cell, and the margin in rclm keeps each
+// range conservative.
 struct ClusterBox {
-  uint32_t u0[3];      // bead 0, fixed point
-  float lo[3], hi[3];  // bounding box relative to bead 0
-  int c0[3];           // cell of bead 0
-  float p0[3];         // bead 0 within its cell
-  bool compact;        // every bead within 3 rcl of bead 0
+  uint32_t u0[3];      // the centre, fixed point
+  float lo[3], hi[3];  // bounding box relative to the centre
+  int c0[3];           // cell of the centre
+  float p0[3];         // the centre within its cell
+  bool compact;        // every bead within 3 rcl of the centre
   float rcl;           // list cutoff, a hair above rc
   float rclm;          // enumeration radius: rcl plus a margin
   int clo[3], chi[3];  // cell ranges relative to c0 (absolute when whole)
@@ -196,7 +202,7 @@ __device__ inline T group_sum(T v) {
 // The geometry from the cluster's bead records, one bead per lane: lane l
 // holds bead l % CI (slots beyond the cluster's beads repeat bead 0), so the
 // bounding box is three lane exchanges per bound.  Receives the lane's bead
-// relative to bead 0 (r) and its squared distance from it (nn).
+// relative to the centre (r) and its squared distance from it (nn).
 template <int CI>
 __device__ inline void make_box(ClusterBox& K, const uint4 me, const RepDesc& R, float r[3], float& nn) {
   const uint32_t u[3] = {me.x, me.y, me.z};
@@ -205,11 +211,15 @@ __device__ inline void make_box(ClusterBox& K, const uint4 me, const RepDesc& R,
   auto upper = [](int a, int b) { return max(a, b); };
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    K.u0[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)u[k]);
-    const int du = (int)(u[k] - K.u0[k]);
-    r[k] = (float)du * R.scalef[k];
-    K.lo[k] = uni((float)__builtin_amdgcn_readfirstlane(group_reduce<CI>(du, lower)) * R.scalef[k]);
-    K.hi[k] = uni((float)__builtin_amdgcn_readfirstlane(group_reduce<CI>(du, upper)) * R.scalef[k]);
+    const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)u[k]);
+    const int du = (int)(u[k] - b0);
+    const int dlo = __builtin_amdgcn_readfirstlane(group_reduce<CI>(du, lower));
+    const int dhi = __builtin_amdgcn_readfirstlane(group_reduce<CI>(du, upper));
+    const int mid = dlo / 2 + dhi / 2;
+    K.u0[k] = b0 + (uint32_t)mid;
+    r[k] = (float)((double)(du - mid) * R.scaled[k]);
+    K.lo[k] = uni((float)(dlo - mid) * R.scalef[k]);
+    K.hi[k] = uni((float)(dhi - mid) * R.scalef[k]);
     const unsigned long long pp = (unsigned long long)K.u0[k] * (unsigned)R.nc[k];
     K.c0[k] = (int)(pp >> 32);
     K.p0[k] = uni((float)(uint32_t)(pp & 0xffffffffu) * 2.3283064365386963e-10f * R.hf[k]);
@@ -410,11 +420,11 @@ __device__ inline void for_chunks(const int* cand, int total, const uint4* __res
 // List build
 // ---------------------------------------------------------------------------
 
-// Whether the cluster takes the fast path: in the frame of bead 0,
-// separations equal the per-pair minimum image for every pair within rc as
-// long as each cluster bead lies within L/2 - rc of bead 0 on each axis (then
-// |d| < rc cannot wrap); and the cluster is compact (every bead within 3 rcl
-// of bead 0), which bounds the rounding of the frame-relative arithmetic.
+// Whether the cluster takes the fast path: in its frame, separations equal the
+// per-pair minimum image for every pair within rc as long as each cluster bead
+// lies within L/2 - rc of the centre on each axis (then |d| < rc cannot wrap);
+// and the cluster is compact (every bead within 3 rcl of the centre), which
+// bounds the rounding of the frame-relative arithmetic.
 __device__ inline bool in_frame(const ClusterBox& K, const RepDesc& R) {
   bool frame = K.compact;
 #pragma unroll
@@ -424,10 +434,10 @@ __device__ inline bool in_frame(const ClusterBox& K, const RepDesc& R) {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// The list test of a compact cluster in bead 0's frame, on the matrix cores:
+// The list test of a compact cluster in its frame, on the matrix cores:
 // |D - r_i|^2 < rcl^2 for some bead i is tested as
 // min_i(|r_i|^2 - 2 D.r_i) < rcl^2 - |D|^2, D the candidate's position
-// relative to bead 0.  The left side is a product of the CI x 3 matrix of
+// relative to the centre.  The left side is a product of the CI x 3 matrix of
 // -2 r_i with the 3 x 64 matrix of the candidates, started from |r_i|^2: the
 // 4 x 4 x 1 multiply in 16 blocks takes four beads (rows) against the
 // wavefront's 64 candidates (four columns in each block) for one axis, and
@@ -435,7 +445,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // per four beads replace 12 fused multiply-adds, and the matrix pipe runs
 // beside the other wavefronts' vector instructions: the candidate test of
 // eight beads went from 35 vector instructions to 8 and 6 matrix
-// instructions.  The candidates that can pass lie within 4 rcl of bead 0, so
+// instructions.  The candidates that can pass lie within 4 rcl of the centre, so
 // the rounding of the expanded form stays below 1e-5 rcl^2, inside the margin
 // of rcl over rc: no pair within rc is dropped.
 template <int CI>
@@ -468,13 +478,13 @@ __device__ inline f32x4 frame_mfma(float q, float d, f32x4 c) {
 }
 
 // Every lane of the wavefront must call it; D receives the lane's candidate
-// pj relative to bead 0.
+// pj relative to the centre.
 template <int CI>
 __device__ inline bool near_frame(const FrameTest<CI>& T, const ClusterBox& K, const uint4& pj, const RepDesc& R,
                                   float& Dx, float& Dy, float& Dz) {
-  Dx = (float)(int)(pj.x - K.u0[0]) * R.scalef[0];
-  Dy = (float)(int)(pj.y - K.u0[1]) * R.scalef[1];
-  Dz = (float)(int)(pj.z - K.u0[2]) * R.scalef[2];
+  Dx = (float)((double)(int)(pj.x - K.u0[0]) * R.scaled[0]);
+  Dy = (float)((double)(int)(pj.y - K.u0[1]) * R.scaled[1]);
+  Dz = (float)((double)(int)(pj.z - K.u0[2]) * R.scaled[2]);
   const float thr = T.rcl2 - (Dx * Dx + Dy * Dy + Dz * Dz);
   f32x4 v = frame_mfma<CI, 0>(T.qx, Dx, T.n[0]);
   v = frame_mfma<CI, 0>(T.qy, Dy, v);
@@ -976,8 +986,8 @@ void k_pair_fused(PairLaunch a) {
     // multiple of 64 here (every drain but the last takes exactly 64), so the
     // entries do not wrap.
     constexpr int G = CI < 4 ? CI : 4;
-    // In single precision, with the cluster in bead 0's frame, the ring holds
-    // the candidate's position relative to bead 0 as floats (computed once,
+    // In single precision, with the cluster in its frame, the ring holds the
+    // candidate's position relative to the centre as floats (computed once,
     // by the test), so a pair costs one subtraction per axis.  Otherwise it
     // holds the fixed-point record, and each pair takes its own minimum
     // image.  (Not for the electrostatics, whose pair cost that would hardly
@@ -991,9 +1001,9 @@ void k_pair_fused(PairLaunch a) {
     FrameTest<CI> ft;
     if (frame) frame_test_init<CI>(ft, K, rme, nn);
     if (REL && frame) {
-      const float rxi = (float)(int)(mi.x - K.u0[0]) * R.scalef[0];
-      const float ryi = (float)(int)(mi.y - K.u0[1]) * R.scalef[1];
-      const float rzi = (float)(int)(mi.z - K.u0[2]) * R.scalef[2];
+      const float rxi = (float)((double)(int)(mi.x - K.u0[0]) * R.scaled[0]);
+      const float ryi = (float)((double)(int)(mi.y - K.u0[1]) * R.scaled[1]);
+      const float rzi = (float)((double)(int)(mi.z - K.u0[2]) * R.scaled[2]);
       // The slots past the last entry of the final drain are filled with a
       // record 1e18 away: the branch-free excluded-volume pair multiplies
       // every lane's separation by its (zero) force factor, so no slot may
