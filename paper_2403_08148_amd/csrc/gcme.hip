@@ -177,6 +177,9 @@ struct gcme_ctx {
   DevBuf part[N_SLOTS], adjp[2];
   DevBuf d_off[N_SLOTS], d_adj_off[2];
   DevBuf d_consts, d_Avals, d_dself;
+  // k_finalize: blocks per replica, their sums and finished counts
+  int fin_nb = 1;
+  DevBuf fin_part, fin_count;
   // per-bead radius derivatives (sorted order) and the self term's factor
   DevBuf dbead_g, dbead_q, d_self_a;
   bool per_bead = false;
@@ -903,6 +906,19 @@ gcme_status build_plan(gcme_handle h) {
     upload(im, h->d_images, s);
   }
 
+  // final sums: a block per 256 partial rows of the largest replica, within
+  // 1,024 blocks in all (a block's rows take one memory latency per 128)
+  {
+    int rows = 0;
+    for (int r = 0; r < R; ++r)
+      rows = std::max(rows, (toff_g[r + 1] - toff_g[r]) + (toff_q[r + 1] - toff_q[r]) + (item_off[r + 1] - item_off[r]) +
+                                (toff_256[r + 1] - toff_256[r]) + (ew_off[r + 1] - ew_off[r]));
+    h->fin_nb = std::max(1, std::min(std::min(64, rows / 256), 1024 / R));
+    HIPCHK(h, h->fin_part.alloc((size_t)R * h->fin_nb * FIN_VALUES * 8));
+    HIPCHK(h, h->fin_count.alloc((size_t)R * 4));
+    HIPCHK(h, hipMemsetAsync(h->fin_count.p, 0, (size_t)R * 4, s));
+  }
+
   // cells
   int nbs = (h->ncells + 1023) / 1024;
   HIPCHK(h, h->counts.alloc((size_t)h->ncells * 4));
@@ -1325,6 +1341,9 @@ void enqueue_outputs(gcme_handle h, hipStream_t s, const gcme_io* io, bool kin) 
     FinalLaunch f{};
     f.rep = h->d_rep.as<RepDesc>();
     f.nrep = h->R;
+    f.nb = h->fin_nb;
+    f.fin_part = h->fin_part.as<double>();
+    f.fin_count = h->fin_count.as<int>();
     for (int sl = 0; sl < N_SLOTS; ++sl) {
       f.part[sl] = h->part[sl].as<double>();
       f.slot_off[sl] = h->d_off[sl].as<int>();

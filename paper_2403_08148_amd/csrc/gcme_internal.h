@@ -536,9 +536,13 @@ void launch_bead_adj_out(hipStream_t s, StateView B, const double* dg, const dou
                          double* out_sigma, double* out_a, int N);
 void launch_state_out(hipStream_t s, StateView A, const RepDesc* rep, double* pos, double* vel,
                       long long ld, int N);
+constexpr int FIN_VALUES = 8 * (N_SLOTS + 4);  // sums per replica: the slots' and 32 of the adjoint
 struct FinalLaunch {
   const RepDesc* rep;
   int nrep;
+  int nb;                        // blocks per replica
+  double* fin_part;              // [nrep * nb][FIN_VALUES], read if nb > 1
+  int* fin_count;                // [nrep] finished blocks; 0 between launches
   const double* part[N_SLOTS];
   const int* slot_off[N_SLOTS];  // [R+1] partial ranges per replica
   const double* consts;          // [R][2]: E_corr, E_self
