@@ -12,25 +12,31 @@ namespace gcme {
 
 namespace {
 
+// Positions to fixed point in the state's order, with the forces cleared;
+// with BIN also the binning (as k_bin) of the new positions.
+template <bool BIN>
 __global__ void k_ingest(const double* __restrict__ pos, long long ld, int N, const RepDesc* __restrict__ rep,
-                         StateView A, long long* F0, long long* F1, long long* F2, int nF) {
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s < nF) {
-    F0[s] = 0;
-    F1[s] = 0;
-    F2[s] = 0;
-  }
-  if (s >= N) return;
-  int id = A.id[s];
-  const RepDesc& R = rep[param_rep(A.param[s])];
+                         StateView A, long long* F, CellView c) {
+  const int s0 = blockIdx.x * blockDim.x + threadIdx.x;
+  const bool active = s0 < N;
+  if (!BIN && !active) return;
+  const int s = active ? s0 : 0;  // (inactive lanes only take part in the binning)
+  const int id = A.id[s];
+  const uint32_t prm = A.param[s];
+  const RepDesc& R = rep[param_rep(prm)];
+  uint32_t u[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     double f = pos[k * ld + id] / R.L[k];
     f -= floor(f);
     // round to the nearest 2^-32 fraction; 2^32 wraps to 0
-    unsigned long long u = (unsigned long long)llrint(f * 4294967296.0);
-    A.pos[k][s] = (uint32_t)u;
+    u[k] = (uint32_t)(unsigned long long)llrint(f * 4294967296.0);
+    if (active) {
+      F[(long long)k * N + s] = 0;
+      A.pos[k][s] = u[k];
+    }
   }
+  if (BIN) bin_bead(c, R, u[0], u[1], u[2], prm, s, id, active);
 }
 
 template <typename I>
@@ -40,13 +46,15 @@ __global__ void k_fill(I* p, I v, long long n) {
   for (; i < n; i += stride) p[i] = v;
 }
 
-__global__ void k_bin(StateView A, const RepDesc* __restrict__ rep, CellView c, int N) {
+// The binning alone, and (F given) the forces cleared.
+__global__ void k_bin(StateView A, const RepDesc* __restrict__ rep, CellView c, long long* F, int N) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   const bool active = s < N;
   const int si = active ? s : 0;
   const uint32_t p = A.param[si];
   const RepDesc& R = rep[param_rep(p)];
   const int id = c.slot_a ? A.id[si] : 0;
+  if (F && active) F[s] = F[(long long)N + s] = F[2LL * N + s] = 0;
   bin_bead(c, R, A.pos[0][si], A.pos[1][si], A.pos[2][si], p, s, id, active);
 }
 
@@ -315,16 +323,116 @@ __global__ void k_permute(StateView A, StateView B, uint4* __restrict__ bpk, Cel
   }
 }
 
-__global__ void k_commit(StateView B, StateView A, int N) {
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= N) return;
+// The whole sort (scan, scatter and permute) in one block, for small systems,
+// where the three launches and the gaps between them take longer than the
+// work: N = 1,536 went from 10 us in three launches, and 12 us between them,
+// to 9 us in one.  The cell counts of all beads (low half) and of the charged
+// ones (high half) are scanned together in LDS; the scattered bead indices
+// stay there too (with a mark for the charged ones), so the ranks within a
+// cell are LDS reads.
+constexpr int SMALL_SORT_THREADS = 1024;
+constexpr int SMALL_SORT_BPT = 4;  // beads per thread
+constexpr int SMALL_SORT_BEADS = SMALL_SORT_THREADS * SMALL_SORT_BPT;
+constexpr int SMALL_SORT_CELLS = 32768;  // 128 KiB of LDS beside the 16 KiB of bead indices
+
+__global__ __launch_bounds__(SMALL_SORT_THREADS) void k_sort_small(StateView A, StateView B, uint4* __restrict__ bpk,
+                                                                   CellView c, ChargedView q, int N) {
+  static_assert(SMALL_SORT_BEADS < 65536, "counts are packed in halves of a word");
+  constexpr int NT = SMALL_SORT_THREADS, BPT = SMALL_SORT_BPT;
+  __shared__ int sh[NT / 64];
+  extern __shared__ __align__(16) int buf[];  // ncells packed counts, then N bead indices
+  const int nc = c.ncells;
+  int* tmp = buf + nc;
+  if (c.step && threadIdx.x == 0) *c.step += 1ULL;
+  // this thread's beads: their cells and all that is moved, requested at once
+  int cid[BPT], id[BPT];
+  uint32_t px[BPT], py[BPT], pz[BPT], prm[BPT];
+  double vx[BPT], vy[BPT], vz[BPT];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    A.pos[k][s] = B.pos[k][s];
-    A.vel[k][s] = B.vel[k][s];
+  for (int u = 0; u < BPT; ++u) {
+    const int s = threadIdx.x + u * NT;
+    const bool on = s < N;
+    cid[u] = on ? c.cell[s] : 0;
+    prm[u] = on ? A.param[s] : 0u;
+    px[u] = on ? A.pos[0][s] : 0u;
+    py[u] = on ? A.pos[1][s] : 0u;
+    pz[u] = on ? A.pos[2][s] : 0u;
+    vx[u] = on ? A.vel[0][s] : 0.0;
+    vy[u] = on ? A.vel[1][s] : 0.0;
+    vz[u] = on ? A.vel[2][s] : 0.0;
+    id[u] = on ? A.id[s] : 0;
   }
-  A.param[s] = B.param[s];
-  A.id[s] = B.id[s];
+  for (int i = threadIdx.x; i < nc; i += NT) {
+    buf[i] = c.counts[i] | c.qcounts[i] << 16;
+    c.counts[i] = c.qcounts[i] = 0;  // for the next binning
+  }
+  __syncthreads();
+  const int per = (nc + NT - 1) / NT;
+  const int lo = min(nc, (int)threadIdx.x * per), hi = min(lo + per, nc);
+  int sum = 0;
+  for (int i = lo; i < hi; ++i) sum += buf[i];
+  const int inc = block_incl_scan<NT>(sum, sh);
+  int run = inc - sum;
+  for (int i = lo; i < hi; ++i) {
+    const int v = buf[i];
+    buf[i] = run;
+    run += v;
+  }
+  if (threadIdx.x == NT - 1) {
+    c.start[nc] = inc & 0xffff;
+    c.qstart[nc] = (unsigned)inc >> 16;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < nc; i += NT) {
+    const unsigned v = (unsigned)buf[i];
+    c.start[i] = (int)(v & 0xffffu);
+    c.qstart[i] = (int)(v >> 16);
+  }
+  __syncthreads();
+  // scatter; each cell's low half counts up to the next cell's start
+#pragma unroll
+  for (int u = 0; u < BPT; ++u) {
+    const int s = threadIdx.x + u * NT;
+    if (s < N) {
+      const int slot = atomicAdd(&buf[cid[u]], 1) & 0xffff;
+      // (slots outside the population cannot come from consistent counts)
+      if (slot < N) tmp[slot] = s | (param_z(prm[u]) != 0 ? 0x10000 : 0);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < BPT; ++u) {
+    const int s = threadIdx.x + u * NT;
+    if (s >= N) continue;
+    const int c0 = cid[u] > 0 ? buf[cid[u] - 1] & 0xffff : 0, c1 = min(buf[cid[u]] & 0xffff, N);
+    int rank = 0, qrank = 0;
+    for (int t = c0; t < c1; ++t) {
+      const int o = tmp[t];
+      const bool before = (o & 0xffff) < s;
+      rank += before;
+      qrank += before && (o & 0x10000);
+    }
+    const int n = c0 + rank;
+    if (n >= N) continue;
+    B.pos[0][n] = px[u];
+    B.pos[1][n] = py[u];
+    B.pos[2][n] = pz[u];
+    B.vel[0][n] = vx[u];
+    B.vel[1][n] = vy[u];
+    B.vel[2][n] = vz[u];
+    B.param[n] = prm[u];
+    B.id[n] = id[u];
+    if (c.slot_of && (unsigned)id[u] < (unsigned)N) c.slot_of[id[u]] = n;
+    const uint4 rec = make_uint4(px[u], py[u], pz[u], prm[u]);
+    bpk[n] = rec;
+    if (param_z(prm[u]) != 0) {
+      const int qn = (int)((unsigned)buf[cid[u]] >> 16) + qrank;
+      if (qn < q.n) {
+        q.pk[qn] = rec;
+        q.idx[qn] = n;
+      }
+    }
+  }
 }
 
 // Column clusters (see ColLaunch).  One block: the columns' cluster counts
@@ -411,12 +519,12 @@ inline int nblk(long long n, int t) { return (int)((n + t - 1) / t); }
 
 }  // namespace
 
-void launch_ingest(hipStream_t s, const double* pos_soa, int N, long long ld, const RepDesc* rep,
-                   const uint32_t* param, StateView A, long long* F, int nF) {
-  (void)param;
-  int n = N > nF ? N : nF;
-  hipLaunchKernelGGL(k_ingest, dim3(nblk(n, 256)), dim3(256), 0, s, pos_soa, ld, N, rep, A, F, F + nF,
-                     F + 2LL * nF, nF);
+void launch_ingest(hipStream_t s, const double* pos_soa, int N, const RepDesc* rep, StateView A, long long* F,
+                   const CellView* bin) {
+  if (bin)
+    hipLaunchKernelGGL(k_ingest<true>, dim3(nblk(N, 256)), dim3(256), 0, s, pos_soa, N, N, rep, A, F, *bin);
+  else
+    hipLaunchKernelGGL(k_ingest<false>, dim3(nblk(N, 256)), dim3(256), 0, s, pos_soa, N, N, rep, A, F, CellView{});
 }
 
 void launch_fill_i64(hipStream_t s, long long* p, long long v, long long n) {
@@ -426,11 +534,11 @@ void launch_fill_i64(hipStream_t s, long long* p, long long v, long long n) {
   hipLaunchKernelGGL(k_fill<long long>, dim3(b), dim3(256), 0, s, p, v, n);
 }
 
-void launch_bin(hipStream_t s, StateView A, const RepDesc* rep, CellView c, int N) {
-  hipLaunchKernelGGL(k_bin, dim3(nblk(N, BEAD_THREADS)), dim3(BEAD_THREADS), 0, s, A, rep, c, N);
+void launch_bin(hipStream_t s, StateView A, const RepDesc* rep, CellView c, long long* F, int N) {
+  hipLaunchKernelGGL(k_bin, dim3(nblk(N, BEAD_THREADS)), dim3(BEAD_THREADS), 0, s, A, rep, c, F, N);
 }
 
-void launch_scan(hipStream_t s, CellView c) {
+static void launch_scan(hipStream_t s, CellView c) {
   if (c.ncells <= SINGLE_SCAN_MAX) {
     const size_t sh = (size_t)c.ncells * 4;
     if (sh > 65536) (void)hipFuncSetAttribute((const void*)k_scan_single, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
@@ -447,11 +555,15 @@ void launch_scan(hipStream_t s, CellView c) {
   hipLaunchKernelGGL(k_scan_apply<false>, dim3(nb), dim3(SCAN_THREADS), 0, s, c, nb);
 }
 
-void launch_scatter(hipStream_t s, CellView c, int N) {
+void launch_sort(hipStream_t s, StateView A, StateView B, uint4* bpk, CellView c, ChargedView q, int N) {
+  if (N <= SMALL_SORT_BEADS && c.ncells <= SMALL_SORT_CELLS) {
+    const size_t sh = ((size_t)c.ncells + N) * 4;
+    if (sh > 65536) (void)hipFuncSetAttribute((const void*)k_sort_small, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+    hipLaunchKernelGGL(k_sort_small, dim3(1), dim3(SMALL_SORT_THREADS), sh, s, A, B, bpk, c, q, N);
+    return;
+  }
+  launch_scan(s, c);
   hipLaunchKernelGGL(k_scatter, dim3(nblk(N, BEAD_THREADS)), dim3(BEAD_THREADS), 0, s, c, N);
-}
-
-void launch_permute(hipStream_t s, StateView A, StateView B, uint4* bpk, CellView c, ChargedView q, int N) {
   hipLaunchKernelGGL(k_permute, dim3(nblk(N, BEAD_THREADS)), dim3(BEAD_THREADS), 0, s, A, B, bpk, c, q, N);
 }
 
@@ -465,10 +577,6 @@ void launch_col_clusters(hipStream_t s, const ColLaunch& a) {
   const bool fill = a.ncols <= COL_THREADS;
   hipLaunchKernelGGL(k_col_scan, dim3(1), dim3(COL_THREADS), sh, s, a, fill);
   if (!fill) hipLaunchKernelGGL(k_col_fill, dim3(nblk(a.ncols, 128)), dim3(128), 0, s, a);
-}
-
-void launch_commit(hipStream_t s, StateView B, StateView A, int N) {
-  hipLaunchKernelGGL(k_commit, dim3(nblk(N, 256)), dim3(256), 0, s, B, A, N);
 }
 
 }  // namespace gcme

@@ -151,7 +151,12 @@ struct gcme_ctx {
   std::vector<int> nq, qoff;
   int NQ = 0;
   // tuning
-  gcme_tuning tune{3, 8, 4, 50, 3, 0, 0, 0, 0, 0, 0};  // list-free pairs, three stream branches, 4 x 4 mesh tiles
+  // list-free pairs, 4 x 4 mesh tiles, the mesh chain on the context's stream
+  // and the pairs on a second (layout 2; steps in us against three branches,
+  // layout 0: N = 4,099 59 / 71, 16,000 73 / 88, 32,768 77 / 87, in FP64 67 / 77,
+  // 84 / 104 and 106 / 111; the adsorption study's slabs 845 / 916 and 743 / 786
+  // for four; N = 2,097,152 alike)
+  gcme_tuning tune{3, 8, 4, 50, 3, 2, 0, 0, 0, 0, 0};
   bool plan_dirty = true;
   // device buffers
   DevBuf a_pos[3], a_vel[3], a_param, a_id;
@@ -308,6 +313,7 @@ ChargedView qview(gcme_handle h) {
   ChargedView q;
   q.pk = h->q_pk.as<uint4>();
   q.idx = h->q_idx.as<int>();
+  q.n = h->NQ;
   return q;
 }
 
@@ -1235,15 +1241,20 @@ void enqueue_elec_pairs(gcme_handle h, hipStream_t s, bool ev, bool adj) {
   launch_pair_elec(s, q, h->fp64, ev, adj);
 }
 
-// Sort the state A into B by cell (and the charged copy), on stream s;
-// bin = false when the integrator has already binned A.
-void enqueue_sort(gcme_handle h, hipStream_t s, bool bin = true) {
+// Sort the state A into B by cell (and the charged copy), on stream s.
+enum SortOf {
+  SORT_BIN,     // A is binned first
+  SORT_CLEAR,   // ... and the forces cleared
+  SORT_BINNED,  // A was binned with its new positions (launch_ingest)
+  SORT_STEP     // ... by the integrator: this sort starts the next step, and
+                // its scan advances the step counter
+};
+void enqueue_sort(gcme_handle h, hipStream_t s, SortOf of) {
   // counts are left cleared by the previous permute (and at plan build)
   CellView c = cview(h);
-  // a step's sort (after the integrator's binning) starts the next step:
-  // its scan advances the step counter
-  if (!bin) c.step = h->d_step.as<unsigned long long>();
-  if (bin) launch_bin(s, viewA(h), h->d_rep.as<RepDesc>(), c, h->N);
+  if (of == SORT_STEP) c.step = h->d_step.as<unsigned long long>();
+  if (of == SORT_BIN || of == SORT_CLEAR)
+    launch_bin(s, viewA(h), h->d_rep.as<RepDesc>(), c, of == SORT_CLEAR ? h->F.as<long long>() : nullptr, h->N);
   if (h->nimages > 0) {
     ImageLaunch im{};
     im.rep = h->d_rep.as<RepDesc>();
@@ -1253,17 +1264,24 @@ void enqueue_sort(gcme_handle h, hipStream_t s, bool bin = true) {
     im.status = h->d_status.as<unsigned>();
     launch_images(s, im, viewA(h), c);
   }
-  launch_scan(s, c);
-  launch_scatter(s, c, h->N);
-  launch_permute(s, viewA(h), viewB(h), h->b_pk.as<uint4>(), c, qview(h), h->N);
+  launch_sort(s, viewA(h), viewB(h), h->b_pk.as<uint4>(), c, qview(h), h->N);
 }
+
+// Evaluations launched directly (not from a graph) run their three parts in
+// sequence on the context's stream up to this many beads: the fork and the
+// joins are seven event calls of the host, 70 us, where all the launches of a
+// small evaluation take 20.  Passes in sequence against three streams, in us:
+// 300 beads 124 / 158, 4,000 134 / 159 (FP64 125 / 149), 8,000 150 / 167;
+// waited for one by one 157 / 165, 171 / 161 (191 / 173), 184 / 188; from
+// 16,000 beads on a single evaluation is longer in sequence (228 / 191).
+constexpr int ONE_STREAM_BEADS = 4096;
 
 // Forces (and partial sums if ev) on the sorted copy B; F must be cleared.
 // The excluded-volume kernel, the charged real-space kernel and the mesh
 // chain are independent and all add into the integer force accumulator, so
 // they run as three concurrent branches (fork/join with events; captured as
 // parallel graph branches).
-void enqueue_forces(gcme_handle h, hipStream_t s, bool ev, bool adj) {
+void enqueue_forces(gcme_handle h, hipStream_t s, bool ev, bool adj, bool one_stream = false) {
   if (h->NQ == 0) {
     enqueue_gcm_pairs(h, s, ev, adj);
     launch_bonds(s, bond_args(h), viewB(h));
@@ -1285,7 +1303,7 @@ void enqueue_forces(gcme_handle h, hipStream_t s, bool ev, bool adj) {
   // a context without auxiliary streams (the no-alloc entry point's) runs
   // the three parts in sequence on s
   static const Layout kSingle = {0, 0, 0, "gqp"};
-  const Layout& L = h->aux[0] ? kLayouts[h->tune.stream_layout] : kSingle;
+  const Layout& L = h->aux[0] && !one_stream ? kLayouts[h->tune.stream_layout] : kSingle;
   hipStream_t st3[3] = {s, h->aux[0], h->aux[1]};
   hipStream_t sg = st3[L.g], sq = st3[L.q], sp = st3[L.p];
   const bool use1 = L.g == 1 || L.q == 1 || L.p == 1, use2 = L.g == 2 || L.q == 2 || L.p == 2;
@@ -1333,12 +1351,22 @@ void enqueue_forces(gcme_handle h, hipStream_t s, bool ev, bool adj) {
   }
 }
 
-void enqueue_outputs(gcme_handle h, hipStream_t s, const gcme_io* io, bool kin) {
-  long long* const F3[3] = {Fk(h, 0), Fk(h, 1), Fk(h, 2)};
-  if (io->force) launch_forces_out(s, viewB(h), F3, io->force, h->N, h->N, 1.0 / h->fscale());
+// The outputs io asks for (null: none) from B and the partial sums, and with
+// commit the copy of B to A.
+void enqueue_outputs(gcme_handle h, hipStream_t s, const gcme_io* io, bool kin, bool commit) {
+  static const gcme_io none{};
+  if (!io) io = &none;
+  OutLaunch o{};
+  o.B = viewB(h);
+  o.A = viewA(h);
+  o.F = h->F.as<long long>();
+  o.force = io->force;
+  o.commit = commit ? 1 : 0;
+  o.N = h->N;
+  o.fscale_inv = 1.0 / h->fscale();
   bool adj = io->dE_dA || io->dE_dsigma || io->dE_da;
   if (io->energy || io->virial || adj) {
-    FinalLaunch f{};
+    FinalLaunch& f = o.fin;
     f.rep = h->d_rep.as<RepDesc>();
     f.nrep = h->R;
     f.nb = h->fin_nb;
@@ -1379,8 +1407,8 @@ void enqueue_outputs(gcme_handle h, hipStream_t s, const gcme_io* io, bool kin) 
     f.dE_da = io->dE_da;
     f.adj_scale = io->force_vjp ? 2.0 : 1.0;
     f.vjp = io->force_vjp ? 1 : 0;
-    launch_finalize(s, f);
   }
+  launch_outputs(s, o);
 }
 
 gcme_status check_ready(gcme_handle h) {
@@ -1403,9 +1431,9 @@ gcme_status check_ready(gcme_handle h) {
   return GCME_OK;
 }
 
-// One full evaluation on stream s: sort, forces, commit B -> A.
+// One full evaluation of the state's positions on stream s: clear, sort, forces.
 void enqueue_eval(gcme_handle h, hipStream_t s, bool ev, bool adj) {
-  enqueue_sort(h, s);
+  enqueue_sort(h, s, SORT_CLEAR);
   enqueue_forces(h, s, ev, adj);
 }
 
@@ -1419,7 +1447,7 @@ void enqueue_eval(gcme_handle h, hipStream_t s, bool ev, bool adj) {
 void enqueue_step_rest(gcme_handle h, hipStream_t s, bool between, bool ev) {
   IntLaunch ia = int_args(h);
   long long* const F3[3] = {Fk(h, 0), Fk(h, 1), Fk(h, 2)};
-  enqueue_sort(h, s, false);
+  enqueue_sort(h, s, SORT_STEP);
   enqueue_forces(h, s, ev, false);
   ia.stamps = stamps_for(h, ST_INT_LAST);
   if (between)
@@ -1452,9 +1480,8 @@ gcme_status prepare_graphs(gcme_handle h) {
 
 gcme_status ensure_forces(gcme_handle h) {
   if (h->forces_valid) return GCME_OK;
-  launch_fill_i64(h->stream, h->F.as<long long>(), 0, 3LL * h->N);
   enqueue_eval(h, h->stream, false, false);
-  launch_commit(h->stream, viewB(h), viewA(h), h->N);
+  enqueue_outputs(h, h->stream, nullptr, false, true);
   HIPCHK(h, hipGetLastError());
   h->forces_valid = true;
   return GCME_OK;
@@ -1789,7 +1816,7 @@ gcme_status gcme_set_state(gcme_handle h, const double* pos, const double* vel, 
   h->images_checked = h->images.empty();
   gcme_status st = build_plan(h);
   if (st != GCME_OK) return st;
-  launch_ingest(h->stream, pos, N, N, h->d_rep.as<RepDesc>(), nullptr, viewA(h), h->F.as<long long>(), N);
+  launch_ingest(h->stream, pos, N, h->d_rep.as<RepDesc>(), viewA(h), h->F.as<long long>());
   HIPCHK(h, hipGetLastError());
   HIPCHK(h, hipMemsetAsync(h->d_step.p, 0, 8, h->stream));
   HIPCHK(h, hipStreamSynchronize(h->stream));
@@ -1823,10 +1850,6 @@ gcme_status gcme_forces_energy(gcme_handle h, const gcme_io* io) {
         return fail(h, GCME_EUNSUPPORTED, "dE/da is not provided with the all-reciprocal splitting");
   HIPCHK(h, hipSetDevice(h->device));
   hipStream_t s = h->stream;
-  if (io->pos)
-    launch_ingest(s, io->pos, h->N, h->N, h->d_rep.as<RepDesc>(), nullptr, viewA(h), h->F.as<long long>(), h->N);
-  else
-    launch_fill_i64(s, h->F.as<long long>(), 0, 3LL * h->N);
   const bool pb = io->dE_dsigma_bead || io->dE_da_bead;
   bool adj = io->dE_dA || io->dE_dsigma || io->dE_da || pb;
   if (io->force_vjp && (pb || !adj))
@@ -1836,21 +1859,20 @@ gcme_status gcme_forces_energy(gcme_handle h, const gcme_io* io) {
   if (pb) launch_fill_i64(s, h->dbead_q.as<long long>(), 0, h->N);
   h->per_bead = pb;
   h->vjp = io->force_vjp != nullptr;
-  if (h->vjp) {
-    // v to the sorted order the pair kernels index
-    enqueue_sort(h, s);
-    launch_gather_vjp(s, viewB(h), io->force_vjp, h->vjp_sorted.as<double>(), h->N);
-    enqueue_forces(h, s, ev, adj);
-  } else {
-    enqueue_eval(h, s, ev, adj);
+  if (io->pos) {
+    const CellView c = cview(h);
+    launch_ingest(s, io->pos, h->N, h->d_rep.as<RepDesc>(), viewA(h), h->F.as<long long>(), &c);
   }
+  enqueue_sort(h, s, io->pos ? SORT_BINNED : SORT_CLEAR);
+  // v to the sorted order the pair kernels index
+  if (h->vjp) launch_gather_vjp(s, viewB(h), io->force_vjp, h->vjp_sorted.as<double>(), h->N);
+  enqueue_forces(h, s, ev, adj, h->N <= ONE_STREAM_BEADS);
   h->per_bead = false;
   h->vjp = false;
-  enqueue_outputs(h, s, io, false);
+  enqueue_outputs(h, s, io, false, true);
   if (pb)
     launch_bead_adj_out(s, viewB(h), h->dbead_g.as<double>(), h->dbead_q.as<double>(), h->d_self_a.as<double>(),
                         io->dE_dsigma_bead, io->dE_da_bead, h->N);
-  launch_commit(s, viewB(h), viewA(h), h->N);
   HIPCHK(h, hipGetLastError());
   h->forces_valid = true;
   return GCME_OK;
@@ -1963,7 +1985,7 @@ gcme_status gcme_step(gcme_handle h, int32_t n_steps, const gcme_io* observe) {
   HIPCHK(h, hipGraphLaunch(*last, h->stream));
   if (obs) {
     // the step left A == B (same order); outputs read B and the partials
-    enqueue_outputs(h, h->stream, observe, true);
+    enqueue_outputs(h, h->stream, observe, true, false);
     HIPCHK(h, hipGetLastError());
   }
   h->step += (uint64_t)n_steps;
@@ -2057,7 +2079,7 @@ gcme_status gcme_count_pairs(gcme_handle h, uint64_t* n_pairs) {
   if (st != GCME_OK) return st;
   HIPCHK(h, hipSetDevice(h->device));
   hipStream_t s = h->stream;
-  enqueue_sort(h, s);
+  enqueue_sort(h, s, SORT_BIN);
   HIPCHK(h, hipMemsetAsync(h->d_pairs.p, 0, 8, s));
   PairLaunch g = pair_args(h, false);
   g.pair_count = h->d_pairs.as<unsigned long long>();
@@ -2113,7 +2135,6 @@ gcme_status gcme_autotune(gcme_handle h) {
           if (build_plan(h) != GCME_OK) continue;
           float ms = 0;
           for (int rep = 0; rep < 3; ++rep) {
-            launch_fill_i64(s, h->F.as<long long>(), 0, 3LL * h->N);
             (void)hipEventRecord(e0, s);
             enqueue_eval(h, s, false, false);
             (void)hipEventRecord(e1, s);
@@ -2146,7 +2167,6 @@ gcme_status gcme_autotune(gcme_handle h) {
         if ((pass == 0 ? h->mtx : h->gtx) != sh[0] || (pass == 0 ? h->mty : h->gty) != sh[1]) continue;
         float ms = 0;
         for (int rep = 0; rep < 3; ++rep) {
-          launch_fill_i64(s, h->F.as<long long>(), 0, 3LL * h->N);
           (void)hipEventRecord(e0, s);
           enqueue_eval(h, s, false, false);
           (void)hipEventRecord(e1, s);
@@ -2288,7 +2308,7 @@ gcme_status gcme_profile_step(gcme_handle h, int32_t n_reps, double* ms) {
   }
   HIPCHK(h, sF.alloc(N * 24));
   HIPCHK(h, hipMemcpyAsync(sF.p, h->F.p, N * 24, hipMemcpyDeviceToDevice, s));
-  enqueue_sort(h, s);
+  enqueue_sort(h, s, SORT_BIN);
   IntLaunch ia = int_args(h);
   long long* const F3[3] = {Fk(h, 0), Fk(h, 1), Fk(h, 2)};
   PairLaunch g = pair_args(h, false);
@@ -2297,7 +2317,7 @@ gcme_status gcme_profile_step(gcme_handle h, int32_t n_reps, double* ms) {
   auto stage = [&](int i, hipStream_t st2) {
     switch (i) {
       case 0: launch_int_first(st2, ia, viewA(h), F3); break;
-      case 1: enqueue_sort(h, st2); break;
+      case 1: enqueue_sort(h, st2, SORT_BIN); break;
       case 2:
         if (half_gcm(h, false))
           launch_col_clusters(st2, col_args(h, false));
@@ -2348,7 +2368,6 @@ gcme_status gcme_profile_step(gcme_handle h, int32_t n_reps, double* ms) {
     if (h->yx_fused && (i == 7 || i == 9)) continue;
     // one full evaluation first, so a stage that works in place (the mesh
     // passes) starts from the data a step would give it
-    launch_fill_i64(s, h->F.as<long long>(), 0, 3LL * h->N);
     enqueue_eval(h, s, false, false);
     hipGraph_t gr = nullptr;
     hipGraphExec_t ex = nullptr;
@@ -2358,7 +2377,6 @@ gcme_status gcme_profile_step(gcme_handle h, int32_t n_reps, double* ms) {
     HIPCHK(h, hipGraphInstantiate(&ex, gr, nullptr, nullptr, 0));
     (void)hipGraphDestroy(gr);
     HIPCHK(h, hipGraphLaunch(ex, s));
-    launch_fill_i64(s, h->F.as<long long>(), 0, 3LL * h->N);
     enqueue_eval(h, s, false, false);
     HIPCHK(h, hipEventRecord(e0, s));
     HIPCHK(h, hipGraphLaunch(ex, s));

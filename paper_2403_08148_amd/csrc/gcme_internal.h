@@ -282,6 +282,7 @@ __device__ inline void wave_stamp(unsigned long long* st, int end) {
 struct ChargedView {
   uint4* pk;         // charged beads in cell order
   int* idx;          // sorted bead index of each charged bead
+  int n;             // charged beads
 };
 
 // extra.hip: the slab correction and harmonic bonds, both added to F.
@@ -330,14 +331,16 @@ void launch_bonds(hipStream_t s, const BondLaunch& a, StateView B);
 // ---------------------------------------------------------------------------
 
 // cells.hip
-void launch_ingest(hipStream_t s, const double* pos_soa, int N, long long ld, const RepDesc* rep,
-                   const uint32_t* param, StateView A, long long* F, int nF);
+// New positions to A's order (SoA doubles [3][N] in original order) with the
+// forces cleared, and with bin != null their binning.
+void launch_ingest(hipStream_t s, const double* pos_soa, int N, const RepDesc* rep, StateView A, long long* F,
+                   const CellView* bin = nullptr);
 void launch_fill_i64(hipStream_t s, long long* p, long long v, long long n);
-void launch_bin(hipStream_t s, StateView A, const RepDesc* rep, CellView c, int N);
-void launch_scan(hipStream_t s, CellView c);
-void launch_scatter(hipStream_t s, CellView c, int N);
-void launch_permute(hipStream_t s, StateView A, StateView B, uint4* bpk, CellView c, ChargedView q, int N);
-void launch_commit(hipStream_t s, StateView B, StateView A, int N);
+// The binning of A, with the forces F (if not null) cleared.
+void launch_bin(hipStream_t s, StateView A, const RepDesc* rep, CellView c, long long* F, int N);
+// A, binned, into cell order in B, with the packed records and the charged
+// beads' copies.
+void launch_sort(hipStream_t s, StateView A, StateView B, uint4* bpk, CellView c, ChargedView q, int N);
 
 // pair.hip
 // A cluster is CI consecutive beads of the sorted population (all beads, or
@@ -525,8 +528,6 @@ void launch_int_between(hipStream_t s, const IntLaunch& a, StateView B, StateVie
                         const CellView& bin);
 void launch_int_last(hipStream_t s, const IntLaunch& a, StateView B, StateView A,
                      long long* const F[3], bool kin);
-void launch_forces_out(hipStream_t s, StateView B, long long* const F[3], double* out, long long ld,
-                       int N, double fscale_inv);
 // v (original order, [3][N]) to sorted order for the force vector-Jacobian
 // product.
 void launch_gather_vjp(hipStream_t s, StateView B, const double* v, double* vs, int N);
@@ -560,6 +561,18 @@ struct FinalLaunch {
                                  // product (its pair sums are not halved)
   int vjp;                       // the adjoint holds sum_i v_i . dF_i/dtheta
 };
-void launch_finalize(hipStream_t s, const FinalLaunch& a);
+// The outputs of an evaluation or run in one launch: the energy, virial and
+// parameter derivatives (fin.nb > 0), the forces in original order (force not
+// null) and the copy of B to A (commit).
+struct OutLaunch {
+  FinalLaunch fin;
+  StateView B, A;
+  const long long* F;  // [3][N]
+  double* force;       // [3][N] or null
+  int commit;
+  int N;
+  double fscale_inv;
+};
+void launch_outputs(hipStream_t s, const OutLaunch& a);
 
 }  // namespace gcme

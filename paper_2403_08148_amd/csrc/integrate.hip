@@ -209,16 +209,6 @@ __global__ __launch_bounds__(256) void k_int_last(IntLaunch a, StateView B, Stat
   wave_stamp(a.stamps, 1);
 }
 
-__global__ void k_forces_out(StateView B, long long* F0, long long* F1, long long* F2, double* out, long long ld,
-                             int N, double sc) {
-  int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
-  int id = B.id[n];
-  out[id] = (double)F0[n] * sc;
-  out[ld + id] = (double)F1[n] * sc;
-  out[2 * ld + id] = (double)F2[n] * sc;
-}
-
 __global__ void k_gather_vjp(StateView B, const double* v, double* vs, int N) {
   const int n = blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= N) return;
@@ -272,11 +262,11 @@ __device__ inline double row_sum(const double* part, int lo, int hi, int first, 
 // depend on which one that is.  (One block with a block sum per slot and
 // column took 20 us at N = 300 and 74 us for the 12,500 rows of N = 200,000;
 // now 4 and 7 us.)
-__global__ __launch_bounds__(256) void k_finalize(FinalLaunch a) {
+__device__ inline void finalize_block(const FinalLaunch& a, int bid) {
   __shared__ double sh[4][FIN_VALUES];
   __shared__ double res[FIN_VALUES];
   __shared__ int last;
-  const int r = blockIdx.x / a.nb, b = blockIdx.x % a.nb;
+  const int r = bid / a.nb, b = bid % a.nb;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int col = lane & 7, first = b * 32 + (threadIdx.x >> 3), step = 32 * a.nb;
   const bool adj = a.dE_dA || a.dE_dsigma || a.dE_da;
@@ -309,7 +299,7 @@ __global__ __launch_bounds__(256) void k_finalize(FinalLaunch a) {
   __syncthreads();
   for (int k = threadIdx.x; k < FIN_VALUES; k += 256) {
     res[k] = (sh[0][k] + sh[1][k]) + (sh[2][k] + sh[3][k]);
-    if (a.nb > 1) a.fin_part[(size_t)blockIdx.x * FIN_VALUES + k] = res[k];
+    if (a.nb > 1) a.fin_part[(size_t)bid * FIN_VALUES + k] = res[k];
   }
   if (a.nb > 1) {
     __threadfence();  // this block's sums before its count
@@ -365,6 +355,32 @@ __global__ __launch_bounds__(256) void k_finalize(FinalLaunch a) {
   }
 }
 
+// The first blocks take the final sums, the others 256 beads each.
+__global__ __launch_bounds__(256) void k_outputs(OutLaunch a) {
+  const int nfin = a.fin.nrep * a.fin.nb;
+  if ((int)blockIdx.x < nfin) {
+    finalize_block(a.fin, blockIdx.x);
+    return;
+  }
+  const int n = ((int)blockIdx.x - nfin) * 256 + (int)threadIdx.x;
+  if (n >= a.N) return;
+  const int id = a.B.id[n];
+  const size_t N = (size_t)a.N;
+  if (a.force) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) a.force[k * N + id] = (double)a.F[k * N + n] * a.fscale_inv;
+  }
+  if (a.commit) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      a.A.pos[k][n] = a.B.pos[k][n];
+      a.A.vel[k][n] = a.B.vel[k][n];
+    }
+    a.A.param[n] = a.B.param[n];
+    a.A.id[n] = id;
+  }
+}
+
 inline int nblk(long long n, int t) { return (int)((n + t - 1) / t); }
 
 }  // namespace
@@ -391,12 +407,6 @@ void launch_int_last(hipStream_t s, const IntLaunch& a, StateView B, StateView A
     hipLaunchKernelGGL(k_int_last<false>, dim3(a.ntiles), dim3(256), 0, s, a, B, A, F[0], F[1], F[2]);
 }
 
-void launch_forces_out(hipStream_t s, StateView B, long long* const F[3], double* out, long long ld, int N,
-                       double fscale_inv) {
-  hipLaunchKernelGGL(k_forces_out, dim3(nblk(N, 256)), dim3(256), 0, s, B, F[0], F[1], F[2], out, ld, N,
-                     fscale_inv);
-}
-
 void launch_gather_vjp(hipStream_t s, StateView B, const double* v, double* vs, int N) {
   hipLaunchKernelGGL(k_gather_vjp, dim3(nblk(N, 256)), dim3(256), 0, s, B, v, vs, N);
 }
@@ -411,8 +421,9 @@ void launch_state_out(hipStream_t s, StateView A, const RepDesc* rep, double* po
   hipLaunchKernelGGL(k_state_out, dim3(nblk(N, 256)), dim3(256), 0, s, A, rep, pos, vel, ld, N);
 }
 
-void launch_finalize(hipStream_t s, const FinalLaunch& a) {
-  hipLaunchKernelGGL(k_finalize, dim3(a.nrep * a.nb), dim3(256), 0, s, a);
+void launch_outputs(hipStream_t s, const OutLaunch& a) {
+  const int blocks = a.fin.nrep * a.fin.nb + (a.force || a.commit ? nblk(a.N, 256) : 0);
+  if (blocks > 0) hipLaunchKernelGGL(k_outputs, dim3(blocks), dim3(256), 0, s, a);
 }
 
 }  // namespace gcme

@@ -1,0 +1,58 @@
+"""The sort of small systems in one block (up to 4,096 beads, four per
+thread) and the first size past it, against the FP64 oracle and, for the
+order it leaves the beads in, a run of steps against single steps (bit for
+bit).  Sizes at the edges of its threads' shares; crowded cells (one cell per
+axis), several replicas in one context, and a bead count below one wavefront.
+"""
+import numpy as np
+import pytest
+
+import gcme_workloads as W
+from tests.gpu_common import make_engine, oracle_eval, rel_rms
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"fp64": 1e-9, "mixed": 1e-5}  # the parity tests' force bounds
+
+
+def box_of(n):
+    L = (n / 2.5) ** (1.0 / 3.0)
+    return (1.02 * L, L, L / 1.02)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n", [40, 64, 1023, 1024, 1025, 4095, 4096, 4097])
+def test_small_sort_forces_and_steps(n, precision):
+    box = box_of(n)
+    w = W.small_bulk(N=n, seed=n, box=box, rc=min(2.0, 0.49 * min(box)), grid=(24, 24, 24))
+    ref = oracle_eval(w)
+    eng = make_engine([w], precision)
+    out = eng.forces_energy()
+    eng.sync()
+    assert rel_rms(out["force"].t().cpu().numpy(), ref["F"]) < TOL[precision]
+    states = []
+    for parts in ((5,), (1, 1, 3)):
+        eng.set_state(w.pos, w.type, w.z, w.vel)
+        for k in parts:
+            eng.step(k)
+        pos, vel, step = eng.get_state()
+        eng.sync()
+        assert step == 5
+        states.append((pos.cpu().numpy(), vel.cpu().numpy()))
+    assert np.array_equal(states[0][0], states[1][0]) and np.array_equal(states[0][1], states[1][1])
+    eng.close()
+
+
+def test_small_sort_replicas_and_crowded_cells():
+    ws = [W.small_bulk(N=n, seed=10 + n, box=b, rc=1.9, grid=(16, 16, 16))
+          for n, b in ((700, (3.9, 4.0, 3.8)), (65, (3.8, 3.9, 4.1)), (1300, (8.0, 7.9, 8.2)))]
+    for cells in (1, 4):
+        eng = make_engine(ws, "fp64", tuning=dict(cells_per_cutoff=cells))
+        out = eng.forces_energy()
+        eng.sync()
+        F = out["force"].t().cpu().numpy()
+        off = 0
+        for w in ws:
+            assert rel_rms(F[off:off + w.N], oracle_eval(w)["F"]) < TOL["fp64"]
+            off += w.N
+        eng.close()
