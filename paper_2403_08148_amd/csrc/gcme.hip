@@ -158,6 +158,8 @@ struct gcme_ctx {
   // for four; N = 2,097,152 alike)
   gcme_tuning tune{3, 8, 4, 50, 3, 2, 0, 0, 0, 0, 0};
   bool plan_dirty = true;
+  bool tables_dirty = false;  // only the pair strengths and radii have changed since the plan
+  std::vector<double> zz;     // [R][MAXT] sum of z^2 over the beads of each type
   // device buffers
   DevBuf a_pos[3], a_vel[3], a_param, a_id;
   DevBuf b_pos[3], b_vel[3], b_param, b_id;
@@ -165,7 +167,7 @@ struct gcme_ctx {
   DevBuf b_pk, q_pk, q_idx;
   DevBuf F;
   DevBuf Qc, d_mtiles, d_gtiles;
-  DevBuf d_rep, d_gcm, d_elec, d_adj;
+  DevBuf d_rep;
   DevBuf d_tw, d_rad, d_bsp, d_freq;
   DevBuf d_items[3];
   DevBuf d_cl_g, d_cl_q, d_tiles_g, d_tiles_q, d_tiles_256;
@@ -181,12 +183,21 @@ struct gcme_ctx {
   DevBuf list_g, list_q, cnt_g, cnt_q;
   DevBuf part[N_SLOTS], adjp[2];
   DevBuf d_off[N_SLOTS], d_adj_off[2];
-  DevBuf d_consts, d_Avals, d_dself;
+  // what follows from the pair strengths and radii alone (upload_tables): the
+  // type-pair tables, the energy constants, A, dU_self/da and the self term's
+  // factor, in one buffer and one copy
+  enum { PT_GCM, PT_ELEC, PT_ADJ, PT_CONSTS, PT_AVALS, PT_DSELF, PT_SELF_A, N_PT };
+  DevBuf d_ptab;
+  size_t pt_off[N_PT] = {};
+  template <typename T>
+  T* ptab(int k) const {
+    return reinterpret_cast<T*>(d_ptab.as<char>() + pt_off[k]);
+  }
   // k_finalize: blocks per replica, their sums and finished counts
   int fin_nb = 1;
   DevBuf fin_part, fin_count;
-  // per-bead radius derivatives (sorted order) and the self term's factor
-  DevBuf dbead_g, dbead_q, d_self_a;
+  // per-bead radius derivatives (sorted order)
+  DevBuf dbead_g, dbead_q;
   bool per_bead = false;
   DevBuf vjp_sorted;  // force vector-Jacobian product: v in sorted order
   bool vjp = false;
@@ -347,18 +358,20 @@ std::vector<Tile> make_tiles(const std::vector<int>& off, const std::vector<int>
 // that nearly equal alpha and beta lose no digits.
 void erf_series(double al, double be, double* cphi, double* cg) {
   const double tsp = 2.0 / std::sqrt(M_PI);
-  auto D = [&](int k) {
-    double s = 0;
-    for (int i = 0; i < k; ++i) s += std::pow(al, i) * std::pow(be, k - 1 - i);
-    return (al - be) * s;
-  };
+  // D[k] = (al - be) S_k, S_k = sum_i al^i be^(k-1-i): S_(k+1) = be S_k + al^k
+  double D[2 * NSER + 2], S = 0.0, pw = 1.0;
+  for (int k = 0; k < 2 * NSER + 2; ++k) {
+    D[k] = (al - be) * S;
+    S = be * S + pw;
+    pw *= al;
+  }
   double fact = 1.0;  // n!
   for (int n = 0; n < NSER; ++n) {
     if (n > 0) fact *= n;
     double sgn = (n % 2 == 0) ? 1.0 : -1.0;
-    cphi[n] = tsp * sgn * D(2 * n + 1) / (fact * (2 * n + 1));
+    cphi[n] = tsp * sgn * D[2 * n + 1] / (fact * (2 * n + 1));
     // g: sum_m (-1)^m D(2m+3) 2(m+1) r^{2m} / ((m+1)! (2m+3))
-    cg[n] = tsp * sgn * D(2 * n + 3) * 2.0 * (n + 1) / (fact * (n + 1) * (2 * n + 3));
+    cg[n] = tsp * sgn * D[2 * n + 3] * 2.0 * (n + 1) / (fact * (n + 1) * (2 * n + 3));
   }
 }
 
@@ -415,6 +428,68 @@ void build_tables(gcme_handle h, std::vector<GcmPar<T>>& g, std::vector<ElecPar<
         ad[q].ea = (T)(2.0 / std::sqrt(M_PI) * al / aij);
       }
   }
+}
+
+// The tables that follow from the pair strengths and radii, for every replica,
+// to the device in one copy on the context's stream.  The buffer's size
+// depends on the replica count alone, so its address, which captured step
+// graphs hold, stays.  (A training step sets the parameters of its replicas
+// each time: with the whole plan built again, 46 copies and the host's
+// tables, that took 1.1 ms of the 1.2 ms of a gradient over 8 replicas.)
+gcme_status upload_tables(gcme_handle h) {
+  const int R = h->R;
+  const size_t np = (size_t)R * MAXT * MAXT, nt = (size_t)R * MAXT, ft = h->fp64 ? 8 : 4;
+  const size_t size[gcme_ctx::N_PT] = {np * ft * (sizeof(GcmPar<float>) / 4), np * ft * (sizeof(ElecPar<float>) / 4),
+                                       np * ft * (sizeof(AdjPar<float>) / 4), 2 * (size_t)R * 8, np * 8, nt * 8, nt * 8};
+  size_t total = 0;
+  for (int k = 0; k < gcme_ctx::N_PT; ++k) {
+    h->pt_off[k] = total;
+    total += (size[k] + 255) & ~(size_t)255;
+  }
+  std::vector<unsigned char> host(total, 0);
+  auto put = [&](int k, const void* p, size_t n) { std::memcpy(host.data() + h->pt_off[k], p, std::min(n, size[k])); };
+  auto pair_tables = [&](auto zero) {
+    using T = decltype(zero);
+    std::vector<GcmPar<T>> g;
+    std::vector<ElecPar<T>> e;
+    std::vector<AdjPar<T>> ad;
+    build_tables<T>(h, g, e, ad);
+    put(gcme_ctx::PT_GCM, g.data(), g.size() * sizeof(g[0]));
+    put(gcme_ctx::PT_ELEC, e.data(), e.size() * sizeof(e[0]));
+    put(gcme_ctx::PT_ADJ, ad.data(), ad.size() * sizeof(ad[0]));
+  };
+  static_assert(sizeof(GcmPar<double>) == 2 * sizeof(GcmPar<float>) && sizeof(ElecPar<double>) == 2 * sizeof(ElecPar<float>) &&
+                    sizeof(AdjPar<double>) == 2 * sizeof(AdjPar<float>),
+                "tables of T alone");
+  if (h->fp64)
+    pair_tables(0.0);
+  else
+    pair_tables(0.0f);
+  // constants of eq. ewald: U_corr and U_self, and dU_self/da_t
+  std::vector<double> consts(2 * R, 0.0), Av(np, 0.0), dself(nt, 0.0), sa(nt, 0.0);
+  for (int r = 0; r < R; ++r) {
+    const HostRep& p = h->hp[r];
+    double sz2 = 0, sza = 0;
+    for (int t = 0; t < p.nt; ++t) {
+      const double zz = h->zz[r * MAXT + t];
+      sz2 += zz;
+      sza += zz / p.a[t];
+      sa[r * MAXT + t] = -0.5 * p.lB / (p.a[t] * p.a[t]);
+      dself[r * MAXT + t] = zz * sa[r * MAXT + t];
+      for (int u = 0; u < p.nt; ++u) Av[(size_t)r * MAXT * MAXT + t * MAXT + u] = p.A[t * p.nt + u];
+    }
+    consts[2 * r] = -p.lB * p.beta / std::sqrt(M_PI) * sz2;
+    consts[2 * r + 1] = 0.5 * p.lB * sza;
+  }
+  put(gcme_ctx::PT_CONSTS, consts.data(), consts.size() * 8);
+  put(gcme_ctx::PT_AVALS, Av.data(), Av.size() * 8);
+  put(gcme_ctx::PT_DSELF, dself.data(), dself.size() * 8);
+  put(gcme_ctx::PT_SELF_A, sa.data(), sa.size() * 8);
+  HIPCHK(h, h->d_ptab.alloc(total));
+  HIPCHK(h, hipMemcpyAsync(h->d_ptab.p, host.data(), total, hipMemcpyHostToDevice, h->stream));
+  HIPCHK(h, hipStreamSynchronize(h->stream));  // (the host copy ends here)
+  h->tables_dirty = false;
+  return GCME_OK;
 }
 
 template <typename T>
@@ -622,13 +697,6 @@ gcme_status build_plan(gcme_handle h) {
     upload(tw, h->d_tw, s);
     upload(bsp, h->d_bsp, s);
     upload(frq, h->d_freq, s);
-    std::vector<GcmPar<double>> g;
-    std::vector<ElecPar<double>> e;
-    std::vector<AdjPar<double>> ad;
-    build_tables<double>(h, g, e, ad);
-    upload(g, h->d_gcm, s);
-    upload(e, h->d_elec, s);
-    upload(ad, h->d_adj, s);
     HIPCHK(h, hipStreamSynchronize(s));
   } else {
     std::vector<float> tw, bsp, frq;
@@ -636,13 +704,6 @@ gcme_status build_plan(gcme_handle h) {
     upload(tw, h->d_tw, s);
     upload(bsp, h->d_bsp, s);
     upload(frq, h->d_freq, s);
-    std::vector<GcmPar<float>> g;
-    std::vector<ElecPar<float>> e;
-    std::vector<AdjPar<float>> ad;
-    build_tables<float>(h, g, e, ad);
-    upload(g, h->d_gcm, s);
-    upload(e, h->d_elec, s);
-    upload(ad, h->d_adj, s);
     HIPCHK(h, hipStreamSynchronize(s));
   }
   upload(rad, h->d_rad, s);
@@ -939,9 +1000,8 @@ gcme_status build_plan(gcme_handle h) {
   // half-complex mesh
   HIPCHK(h, h->Qc.alloc((size_t)h->cgrid_total * cs));
 
-  // integrator constants, energy constants
-  std::vector<double> imass(R * MAXT, 1.0), c1(R), c2s(R * MAXT, 0.0), dtv(R), consts(2 * R), Av(R * MAXT * MAXT, 0.0),
-      dself(R * MAXT, 0.0);
+  // integrator constants
+  std::vector<double> imass(R * MAXT, 1.0), c1(R), c2s(R * MAXT, 0.0), dtv(R);
   std::vector<int> lang(R);
   for (int r = 0; r < R; ++r) {
     const HostRep& p = h->hp[r];
@@ -952,33 +1012,16 @@ gcme_status build_plan(gcme_handle h) {
     for (int t = 0; t < p.nt; ++t) {
       imass[r * MAXT + t] = 1.0 / p.mass[t];
       c2s[r * MAXT + t] = std::sqrt((1.0 - cc * cc) * p.kT / p.mass[t]);
-      for (int u = 0; u < p.nt; ++u) Av[(size_t)r * MAXT * MAXT + t * MAXT + u] = p.A[t * p.nt + u];
     }
-    // constants of eq. ewald: U_corr and U_self, and dU_self/da_t
-    double sz2 = 0, sza = 0;
-    for (int i = h->boff[r]; i < h->boff[r] + h->nb[r]; ++i) {
-      double zz = (double)h->h_z[i] * h->h_z[i];
-      int t = h->h_type[i];
-      sz2 += zz;
-      sza += zz / p.a[t];
-      dself[r * MAXT + t] += -0.5 * p.lB * zz / (p.a[t] * p.a[t]);
-    }
-    consts[2 * r] = -p.lB * p.beta / std::sqrt(M_PI) * sz2;
-    consts[2 * r + 1] = 0.5 * p.lB * sza;
   }
   upload(imass, h->d_imass, s);
   upload(c1, h->d_c1, s);
   upload(c2s, h->d_c2s, s);
   upload(dtv, h->d_dt, s);
   upload(lang, h->d_lang, s);
-  upload(consts, h->d_consts, s);
-  upload(Av, h->d_Avals, s);
-  upload(dself, h->d_dself, s);
   {
-    std::vector<double> sa(R * MAXT, 0.0);
-    for (int r = 0; r < R; ++r)
-      for (int t = 0; t < h->hp[r].nt; ++t) sa[r * MAXT + t] = -0.5 * h->hp[r].lB / (h->hp[r].a[t] * h->hp[r].a[t]);
-    upload(sa, h->d_self_a, s);
+    const gcme_status e = upload_tables(h);
+    if (e != GCME_OK) return e;
   }
   upload(h->rep, h->d_rep, s);
   HIPCHK(h, hipStreamSynchronize(s));
@@ -989,9 +1032,9 @@ gcme_status build_plan(gcme_handle h) {
 PairLaunch pair_args(gcme_handle h, bool charged) {
   PairLaunch a{};
   a.rep = h->d_rep.as<RepDesc>();
-  a.gcm = h->d_gcm.p;
-  a.elec = h->d_elec.p;
-  a.adj = h->d_adj.p;
+  a.gcm = h->ptab<void>(gcme_ctx::PT_GCM);
+  a.elec = h->ptab<void>(gcme_ctx::PT_ELEC);
+  a.adj = h->ptab<void>(gcme_ctx::PT_ADJ);
   for (int k = 0; k < 3; ++k) a.F[k] = Fk(h, k);
   a.status = h->d_status.as<unsigned>();
   a.fscale = h->fscale();
@@ -1392,7 +1435,7 @@ void enqueue_outputs(gcme_handle h, hipStream_t s, const gcme_io* io, bool kin, 
     }
     if (!h->any_slab) f.part[SLOT_SLAB] = nullptr;
     if (h->ntiles_b == 0) f.part[SLOT_BOND] = nullptr;
-    f.consts = h->d_consts.as<double>();
+    f.consts = h->ptab<double>(gcme_ctx::PT_CONSTS);
     f.energy = io->energy;
     f.virial = io->virial;
     f.have_kin = kin ? 1 : 0;
@@ -1400,8 +1443,8 @@ void enqueue_outputs(gcme_handle h, hipStream_t s, const gcme_io* io, bool kin, 
     f.adj_part[1] = h->NQ > 0 ? h->adjp[1].as<double>() : nullptr;
     f.adj_off[0] = h->d_adj_off[0].as<int>();
     f.adj_off[1] = h->d_adj_off[1].as<int>();
-    f.Avals = h->d_Avals.as<double>();
-    f.dself = h->d_dself.as<double>();
+    f.Avals = h->ptab<double>(gcme_ctx::PT_AVALS);
+    f.dself = h->ptab<double>(gcme_ctx::PT_DSELF);
     f.dE_dA = io->dE_dA;
     f.dE_dsigma = io->dE_dsigma;
     f.dE_da = io->dE_da;
@@ -1428,6 +1471,7 @@ gcme_status check_ready(gcme_handle h) {
     h->images_checked = true;
   }
   if (h->plan_dirty) return build_plan(h);
+  if (h->tables_dirty) return upload_tables(h);
   return GCME_OK;
 }
 
@@ -1676,8 +1720,15 @@ gcme_status gcme_set_params(gcme_handle h, int32_t replica, const gcme_params* p
   for (int r = 0; r < h->R; ++r)
     if (h->hp[r].set && (r < r0 || r >= r1) && h->hp[r].order != p->order)
       return fail(h, GCME_EUNSUPPORTED, "all replicas must use the same B-spline order");
+  bool pair_only = true;  // nothing but A, sigma and a differs from what is set
   for (int r = r0; r < r1; ++r) {
     HostRep& q = h->hp[r];
+    bool same = q.set && q.kmax == p->kmax && q.rc == p->cutoff && q.beta == beta && q.lB == p->lB && q.kT == p->kT &&
+                q.dt == p->dt && q.gamma == p->gamma && q.order == p->order && q.nt == nt && q.flags == p->flags &&
+                q.bond_k == p->bond_k && q.bond_b == p->bond_b;
+    for (int k = 0; k < 3; ++k) same = same && q.box[k] == p->box[k] && q.K[k] == (p->kmax > 0.0 ? 0 : p->grid[k]);
+    for (int t = 0; t < nt; ++t) same = same && q.mass[t] == (p->mass ? p->mass[t] : 1.0);
+    pair_only = pair_only && same;
     for (int k = 0; k < 3; ++k) {
       q.box[k] = p->box[k];
       q.K[k] = p->kmax > 0.0 ? 0 : p->grid[k];  // no mesh with the exact sum
@@ -1702,7 +1753,10 @@ gcme_status gcme_set_params(gcme_handle h, int32_t replica, const gcme_params* p
     }
     q.set = true;
   }
-  h->plan_dirty = true;
+  if (pair_only)
+    h->tables_dirty = true;
+  else
+    h->plan_dirty = true;
   h->forces_valid = false;
   h->images_checked = h->images.empty();
   if (h->have_state) {
@@ -1775,6 +1829,7 @@ gcme_status gcme_set_state(gcme_handle h, const double* pos, const double* vel, 
   HIPCHK(h, hipMemcpyAsync(zz.data(), z, (size_t)N * 4, hipMemcpyDeviceToHost, h->stream));
   HIPCHK(h, hipStreamSynchronize(h->stream));
   std::vector<int> nq(h->R, 0), qoff(h->R, 0);
+  std::vector<double> zsq((size_t)h->R * MAXT, 0.0);
   int NQ = 0;
   for (int r = 0; r < h->R; ++r) {
     long long net = 0;
@@ -1784,6 +1839,7 @@ gcme_status gcme_set_state(gcme_handle h, const double* pos, const double* vel, 
       if (zz[i] < -127 || zz[i] > 127) return fail(h, GCME_EINVAL, "charge numbers must be in -127..127");
       net += zz[i];
       if (zz[i] != 0) ++nq[r];
+      zsq[r * MAXT + t[i]] += (double)zz[i] * zz[i];
     }
     if (net != 0) return fail(h, GCME_ENONNEUTRAL, "replica " + std::to_string(r) + " is not neutral");
     NQ += nq[r];
@@ -1798,6 +1854,7 @@ gcme_status gcme_set_state(gcme_handle h, const double* pos, const double* vel, 
   h->h_type = t;
   h->h_z = zz;
   h->nq = nq;
+  h->zz = zsq;
   h->qoff = qoff;
   h->NQ = NQ;
   HIPCHK(h, h->q_pk.alloc((size_t)std::max(1, NQ) * 16));
@@ -1871,7 +1928,7 @@ gcme_status gcme_forces_energy(gcme_handle h, const gcme_io* io) {
   h->vjp = false;
   enqueue_outputs(h, s, io, false, true);
   if (pb)
-    launch_bead_adj_out(s, viewB(h), h->dbead_g.as<double>(), h->dbead_q.as<double>(), h->d_self_a.as<double>(),
+    launch_bead_adj_out(s, viewB(h), h->dbead_g.as<double>(), h->dbead_q.as<double>(), h->ptab<double>(gcme_ctx::PT_SELF_A),
                         io->dE_dsigma_bead, io->dE_da_bead, h->N);
   HIPCHK(h, hipGetLastError());
   h->forces_valid = true;
