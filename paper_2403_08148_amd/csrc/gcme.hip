@@ -201,6 +201,7 @@ struct gcme_ctx {
   bool per_bead = false;
   DevBuf vjp_sorted;  // force vector-Jacobian product: v in sorted order
   bool vjp = false;
+  bool want_virial = true;  // of the evaluation being enqueued (observed step graphs keep it)
   DevBuf d_imass, d_c1, d_c2s, d_dt, d_lang;
   DevBuf d_status, d_step, d_pairs;
   DevBuf d_ewk, d_ew_items_s, d_ew_items_f, ew_sp;  // exact reciprocal sums
@@ -1038,6 +1039,7 @@ PairLaunch pair_args(gcme_handle h, bool charged) {
   for (int k = 0; k < 3; ++k) a.F[k] = Fk(h, k);
   a.status = h->d_status.as<unsigned>();
   a.fscale = h->fscale();
+  a.virial = h->want_virial ? 1 : 0;
   if (charged) {
     a.tiles = h->d_tiles_q.as<Tile>();
     a.ntiles = h->ntiles_q;
@@ -1916,6 +1918,7 @@ gcme_status gcme_forces_energy(gcme_handle h, const gcme_io* io) {
   if (pb) launch_fill_i64(s, h->dbead_q.as<long long>(), 0, h->N);
   h->per_bead = pb;
   h->vjp = io->force_vjp != nullptr;
+  h->want_virial = io->virial != nullptr;
   if (io->pos) {
     const CellView c = cview(h);
     launch_ingest(s, io->pos, h->N, h->d_rep.as<RepDesc>(), viewA(h), h->F.as<long long>(), &c);
@@ -1926,6 +1929,7 @@ gcme_status gcme_forces_energy(gcme_handle h, const gcme_io* io) {
   enqueue_forces(h, s, ev, adj, h->N <= ONE_STREAM_BEADS);
   h->per_bead = false;
   h->vjp = false;
+  h->want_virial = true;
   enqueue_outputs(h, s, io, false, true);
   if (pb)
     launch_bead_adj_out(s, viewB(h), h->dbead_g.as<double>(), h->dbead_q.as<double>(), h->ptab<double>(gcme_ctx::PT_SELF_A),

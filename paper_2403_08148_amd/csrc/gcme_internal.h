@@ -366,6 +366,7 @@ struct PairLaunch {
   long long* F[3];
   double* part;        // partial sums of this slot, [ntiles][PART_W]
   double* adj_part;    // adjoint partials [ntiles][MAXT * MAXT + 2 * MAXT]
+  int virial;          // energy variants: the virial is asked for (else its sums stay 0)
   const double* vjp;   // adjoint, or null: v per sorted bead, [3][nbeads]; the
                        // adjoint sums then hold sum_i v_i . dF_i/dtheta
   int nbeads;

@@ -585,11 +585,35 @@ __device__ __attribute__((always_inline)) inline void bracket(const ElecPar<T>& 
   }
 }
 
-// One ordered pair (i, j) with separation d = r_i - r_j, r2 < rc^2.
+// The pair's virial d_a f_b, f = fs d, in FP64.
+template <typename T>
+__device__ inline void add_virial(Lane<T>& L, T fs, T dx, T dy, T dz) {
+  const double fxd = (double)(fs * dx), fyd = (double)(fs * dy), fzd = (double)(fs * dz);
+  L.w0 += fxd * (double)dx;
+  L.w1 += fyd * (double)dy;
+  L.w2 += fzd * (double)dz;
+  L.w3 += fxd * (double)dy;
+  L.w4 += fxd * (double)dz;
+  L.w5 += fyd * (double)dz;
+}
+
+// x to the accumulator of type tj < nt (nt the same for the wavefront: the
+// accumulators of types that the replica does not have are not looked at).
+template <typename T>
+__device__ inline void add_by_type(T (&v)[MAXT], int tj, int nt, T x) {
+#pragma unroll
+  for (int t = 0; t < MAXT; ++t)
+    if (t < nt) v[t] += t == tj ? x : (T)0;
+}
+
+// One ordered pair (i, j) with separation d = r_i - r_j, r2 < rc^2.  The
+// derivative with respect to a radius adds the pair's share at bead i's type
+// alone: bead j's share is added when the pair is seen from j (in the force
+// vector-Jacobian product, whose two visits differ by v, both are added).
 template <typename T, bool ELEC, bool EV, bool ADJ, bool COUNT>
 __device__ inline void interact(Lane<T>& L, T dx, T dy, T dz, T r2, uint32_t pj, const GcmPar<T>* grow,
                                 const ElecPar<T>* erow, const AdjPar<T>* arow, T zi, T beta, T beta2, T lB,
-                                T vx = 0, T vy = 0, T vz = 0, bool vjp = false, T cexpb = 0, T tsb = 0) {
+                                T vx, T vy, T vz, bool vjp, T cexpb, T tsb, int nt, bool vir) {
   const int tj = param_type(pj);
   T fs, en;
   if (!ELEC) {
@@ -610,13 +634,8 @@ __device__ inline void interact(Lane<T>& L, T dx, T dy, T dz, T r2, uint32_t pj,
         duds = vd * en * ap.inv_s2 * ap.s_inv * ((T)9 * r2 * ap.inv_s2 - (T)15);
       }
       L.di += duds * ap.dsig_i;
-#pragma unroll
-      for (int t = 0; t < MAXT; ++t) {
-        if (t == tj) {
-          L.eA[t] += eA;
-          L.dj[t] += duds * ap.dsig_j;
-        }
-      }
+      add_by_type(L.eA, tj, nt, eA);
+      if (vjp) add_by_type(L.dj, tj, nt, duds * ap.dsig_j);
     }
   } else {
     const ElecPar<T>& p = erow[tj];
@@ -634,36 +653,28 @@ __device__ inline void interact(Lane<T>& L, T dx, T dy, T dz, T r2, uint32_t pj,
       // exp(-alpha^2 r^2), so dfs/da_ij = 2 alpha^2 dd
       if (vjp) dd = (vx * dx + vy * dy + vz * dz) * (T)2 * p.alpha2 * dd;
       L.di += dd * ap.daij_i;
-#pragma unroll
-      for (int t = 0; t < MAXT; ++t)
-        if (t == tj) L.dj[t] += dd * ap.daij_j;
+      if (vjp) add_by_type(L.dj, tj, nt, dd * ap.daij_j);
     }
   }
   L.fx += fs * dx;
   L.fy += fs * dy;
   L.fz += fs * dz;
   if (EV) {
-    const double fxd = (double)(fs * dx), fyd = (double)(fs * dy), fzd = (double)(fs * dz);
     L.e += (double)en;
-    L.w0 += fxd * (double)dx;
-    L.w1 += fyd * (double)dy;
-    L.w2 += fzd * (double)dz;
-    L.w3 += fxd * (double)dy;
-    L.w4 += fxd * (double)dz;
-    L.w5 += fyd * (double)dz;
+    if (vir) add_virial(L, fs, dx, dy, dz);
   }
   if (COUNT) ++L.cnt;
 }
 
 // Move the adjoint sums of bead i (type ti) into the per-type accumulators.
 template <typename T, bool ELEC>
-__device__ inline void flush_adj(Lane<T>& L, int ti) {
+__device__ inline void flush_adj(Lane<T>& L, int ti, bool vjp) {
 #pragma unroll
   for (int q = 0; q < MAXT; ++q) {
 #pragma unroll
     for (int t = 0; t < MAXT; ++t)
       if (q == ti && !ELEC) L.ett[q * MAXT + t] += L.eA[t];
-    if (q == ti) L.dsg[q] += L.di;
+    if (q == ti) L.dsg[q] += vjp ? L.di : (T)2 * L.di;  // (both visits' shares; halved at the end)
     L.dsg[q] += L.dj[q];
   }
 #pragma unroll
@@ -688,6 +699,8 @@ struct PairCtx {
   T cexpb, tsb;  // -beta^2 log2(e), (2/sqrt(pi)) beta
   T vx, vy, vz;  // force vector-Jacobian product: v of bead i (adjoint only)
   bool vjp;
+  int nt;        // types of the replica
+  bool vir;      // the virial is asked for
   const ExpPar<T>* prow;
   const GcmPar<T>* grow;
   const ElecPar<T>* erow;
@@ -742,6 +755,8 @@ __device__ inline PairCtx<T> make_ctx(const Tables<T, ELEC, ADJ>& S, const RepDe
   P.grow = S.g + (ELEC ? 0 : ti * MAXT);
   P.erow = S.e + (ELEC ? ti * MAXT : 0);
   P.arow = S.a + (ADJ ? ti * MAXT : 0);
+  P.nt = R.nt;
+  P.vir = a.virial != 0;
   P.vjp = false;
   P.vx = P.vy = P.vz = 0;
   if (ADJ && a.vjp) {
@@ -771,19 +786,12 @@ __device__ inline void pair_at(Lane<T>& L, const PairCtx<T>& P, T dx, T dy, T dz
     L.fy += fs * dy;
     L.fz += fs * dz;
     if (EV) {
-      const T en = P.grow[param_type(pw)].C * ex;
-      const double fxd = (double)(fs * dx), fyd = (double)(fs * dy), fzd = (double)(fs * dz);
-      L.e += (double)en;
-      L.w0 += fxd * (double)dx;
-      L.w1 += fyd * (double)dy;
-      L.w2 += fzd * (double)dz;
-      L.w3 += fxd * (double)dy;
-      L.w4 += fxd * (double)dz;
-      L.w5 += fyd * (double)dz;
+      L.e += (double)(P.grow[param_type(pw)].C * ex);
+      if (P.vir) add_virial(L, fs, dx, dy, dz);
     }
   } else if (in) {
     interact<T, ELEC, EV, ADJ, COUNT>(L, dx, dy, dz, r2, pw, P.grow, P.erow, P.arow, P.zi, P.beta, P.beta2, P.lB,
-                                      P.vx, P.vy, P.vz, P.vjp, P.cexpb, P.tsb);
+                                      P.vx, P.vy, P.vz, P.vjp, P.cexpb, P.tsb, P.nt, P.vir);
   }
 }
 
@@ -809,7 +817,7 @@ __device__ inline void flush_bead(const PairLaunch& a, Lane<T>& L, bool vi, int 
     for (int o = CJ >> 1; o > 0; o >>= 1) d += __shfl_xor(d, o, 64);
     if (vi && jl == 0) a.dbead[ELEC ? a.qidx[i] : i] = (double)d;
   }
-  if (ADJ && vi) flush_adj<T, ELEC>(L, ti);
+  if (ADJ && vi) flush_adj<T, ELEC>(L, ti, a.vjp != nullptr);
   // lanes 0, 1 and 2 of the bead's group add one axis each
   const T fx = group_sum<CJ>(L.fx), fy = group_sum<CJ>(L.fy), fz = group_sum<CJ>(L.fz);
   if (vi && jl < 3) {
