@@ -29,6 +29,25 @@ def _sym(A):
     return 0.5 * (A + A.transpose(-1, -2))
 
 
+def _sym_weights(engine, nt):
+    """The kernel returns dE/dA for each unordered type pair; through the
+    symmetrisation each of the two matrix entries gets half of an off-diagonal
+    value: [nt, nt] of 1 and 1/2, kept with the engine (copied from the host,
+    so complete for every stream)."""
+    kept = engine.__dict__.setdefault("_sym_weights", {})
+    if nt not in kept:
+        kept[nt] = (0.5 * (1.0 + torch.eye(nt, dtype=torch.float64))).to(engine.device)
+    return kept[nt]
+
+
+def _to(device, *tensors):
+    """The tensors on `device`, in one copy."""
+    if all(t.device == device for t in tensors):
+        return tensors
+    flat = torch.cat([t.reshape(-1) for t in tensors]).to(device)
+    return tuple(p.view(t.shape).clone() for p, t in zip(flat.split([t.numel() for t in tensors]), tensors))
+
+
 class GCMeEnergy(torch.autograd.Function):
     """energy[R] = GCMeEnergy.apply(pos, A, a, sigma, engine, params)
 
@@ -68,6 +87,7 @@ class GCMeEnergy(torch.autograd.Function):
         ctx.nt = nt
         ctx.pdev = A.device
         ctx.counts = list(engine.n_beads)
+        ctx.weights = _sym_weights(engine, nt) if need_adj else None
         ctx.save_for_backward(out["force"], *(t for t in (dA, da, ds) if t is not None))
         ctx.has_adj = need_adj
         return E
@@ -79,23 +99,18 @@ class GCMeEnergy(torch.autograd.Function):
         dev = F.device
         gE = gE.to(dev)
         # dE_r/dr_i = -F_i for the beads of replica r
-        per_bead = torch.repeat_interleave(gE, torch.tensor(ctx.counts, device=dev))
-        g_pos = -(F * per_bead.unsqueeze(0)).t()
+        per_bead = -gE
+        if len(ctx.counts) > 1:
+            per_bead = torch.repeat_interleave(per_bead, torch.tensor(ctx.counts, device=dev), output_size=F.shape[1])
+        g_pos = F.t() * per_bead.unsqueeze(1)
         g_A = g_a = g_s = None
         if ctx.has_adj:
             dA, da, ds = saved[1], saved[2], saved[3]
-            # the kernel returns dE/dA for each unordered type pair; through
-            # the symmetrisation each of the two matrix entries gets half of
-            # an off-diagonal value
-            nt = ctx.nt
-            eye = torch.eye(nt, dtype=dA.dtype, device=dev)
-            gA = dA * (0.5 * (1.0 - eye) + eye)
-            g_A = (gA * gE[:, None, None]).to(ctx.pdev)
+            gA = dA * ctx.weights * gE[:, None, None]
             if ctx.tied:
-                g_a = ((da + ds) * gE[:, None]).to(ctx.pdev)
+                g_A, g_a = _to(ctx.pdev, gA, (da + ds) * gE[:, None])
             else:
-                g_a = (da * gE[:, None]).to(ctx.pdev)
-                g_s = (ds * gE[:, None]).to(ctx.pdev)
+                g_A, g_a, g_s = _to(ctx.pdev, gA, da * gE[:, None], ds * gE[:, None])
         return g_pos, g_A, g_a, g_s, None, None
 
 
@@ -139,13 +154,10 @@ class GCMeForces(torch.autograd.Function):
         eng.sync()
         nt = ctx.nt
         dA, da, ds = out["dE_dA"][:, :nt, :nt], out["dE_da"][:, :nt], out["dE_dsigma"][:, :nt]
-        # a type pair's value is for the symmetric parameter: half to each of
-        # the two matrix entries through the symmetrisation
-        eye = torch.eye(nt, dtype=dA.dtype, device=dA.device)
-        g_A = (dA * (0.5 * (1.0 - eye) + eye)).to(ctx.pdev)
+        gA = dA * _sym_weights(eng, nt)
         if ctx.tied:
-            return g_A, (da + ds).to(ctx.pdev), None, None, None, None
-        return g_A, da.to(ctx.pdev), ds.to(ctx.pdev), None, None, None
+            return *_to(ctx.pdev, gA, da + ds), None, None, None, None
+        return *_to(ctx.pdev, gA, da, ds), None, None, None
 
 
 def gcme_forces(engine, params, pos, A, a, sigma=None):
