@@ -759,9 +759,23 @@ gcme_status build_plan(gcme_handle h) {
     t.clear();
     for (int r = 0; r < R; ++r) {
       const RepDesc& d = h->rep[r];
+      // the cell columns of a tile's n mesh lines from t0 on: those that hold
+      // the stencil base points t0 .. t0 + n + order - 2 (mod K)
+      auto columns = [&](int ax, int t0, int n, MeshTile& m) {
+        const long long nc = d.nc[ax], K = d.K[ax];
+        const int lo = (int)((t0 * nc) / K);
+        const int hi = (int)(((long long)(t0 + n + h->order - 1) * nc) / K);
+        m.col0[ax] = hi - lo + 1 >= nc ? 0 : lo;
+        m.ncol[ax] = hi - lo + 1 >= nc ? (int)nc : hi - lo + 1;
+      };
       for (int x = 0; x < d.K[0]; x += ox)
-        for (int y = 0; y < d.K[1]; y += oy)
-          t.push_back(MeshTile{r, x, y, std::min(ox, d.K[0] - x) | (std::min(oy, d.K[1] - y) << 16)});
+        for (int y = 0; y < d.K[1]; y += oy) {
+          const int nx = std::min(ox, d.K[0] - x), ny = std::min(oy, d.K[1] - y);
+          MeshTile m{r, x, y, nx | (ny << 16), {0, 0}, {0, 0}};
+          columns(0, x, nx, m);
+          columns(1, y, ny, m);
+          t.push_back(m);
+        }
     }
     return true;
   };

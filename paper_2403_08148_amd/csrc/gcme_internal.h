@@ -121,10 +121,13 @@ struct LineItem {
 
 // A tile of the mesh for the fused spread / gather passes: the z lines
 // x0 <= x < x0 + nx, y0 <= y < y0 + ny of one replica (nxy = nx | ny << 16).
+// col0, ncol: the cell columns (x, y) that hold every bead whose stencil can
+// meet the tile, col0[d] .. col0[d] + ncol[d] - 1 (mod the cells of the axis).
 struct MeshTile {
   int rep;
   int x0, y0;
   int nxy;
+  int col0[2], ncol[2];
 };
 
 // Tiles of consecutive beads (per-bead kernels) or of consecutive clusters

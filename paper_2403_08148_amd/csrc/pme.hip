@@ -370,8 +370,8 @@ template <typename T, int KC, int LB>
 __global__ __launch_bounds__(FFT_THREADS) void k_fft_y(PmeLaunch a, int inverse) {
   wave_stamp(a.stamps, 0);
   extern __shared__ __align__(16) unsigned char smem[];
-  const LineItem it = a.items[1][xcd_item(blockIdx.x, gridDim.x)];
-  const RepDesc& R = a.rep[it.rep];
+  const LineItem it = uniform_load(a.items[1] + xcd_item(blockIdx.x, a.nitems[1]));
+  const RepDesc R = uniform_load(a.rep + it.rep);
   const int K = KC > 0 ? KC : R.K[1], K2h = R.K2h, K2s = R.K2s, nl = it.count;
   const int LBP = KC > 0 ? LB + 1 : a.lb[1] + 1;
   cplx<T>* A = reinterpret_cast<cplx<T>*>(smem);
@@ -470,9 +470,9 @@ __global__ __launch_bounds__(FFT_THREADS) void k_fft_x_conv(PmeLaunch a) {
   wave_stamp(a.stamps, 0);
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double sh[4];
-  const int item = xcd_item(blockIdx.x, gridDim.x);
-  const LineItem it = a.items[2][item];
-  const RepDesc& R = a.rep[it.rep];
+  const int item = xcd_item(blockIdx.x, a.nitems[2]);
+  const LineItem it = uniform_load(a.items[2] + item);
+  const RepDesc R = uniform_load(a.rep + it.rep);
   const int K = KC > 0 ? KC : R.K[0], K1 = R.K[1], K2h = R.K2h, K2s = R.K2s, nl = it.count;
   const int LBP = KC > 0 ? LB + 1 : a.lb[2] + 1;
   cplx<T>* A = reinterpret_cast<cplx<T>*>(smem);
@@ -685,9 +685,9 @@ __device__ __attribute__((always_inline)) inline void yx_plane(const PmeLaunch& 
 template <typename T, bool EV, int KC, int NT>
 __global__ __launch_bounds__(NT) void k_fft_yx_conv(PmeLaunch a) {
   wave_stamp(a.stamps, 0);
-  const int item = xcd_item(blockIdx.x, gridDim.x);
-  const LineItem it = a.items[0][item];
-  const RepDesc& R = a.rep[it.rep];
+  const int item = xcd_item(blockIdx.x, a.nitems[0]);
+  const LineItem it = uniform_load(a.items[0] + item);
+  const RepDesc R = uniform_load(a.rep + it.rep);
   if constexpr (KC > 0) {
     yx_plane<T, EV, KC, NT>(a, it, R, item);
   } else {
@@ -721,44 +721,19 @@ __device__ inline int block_scan_incl(int v, int* sh) {
   return v + add;
 }
 
-// Charged beads whose order-P stencil can meet a mesh tile: whole cell
-// columns (all z) of the charged cell list over the cell range that holds
-// the stencil base points k0 in [t0, t0 + n + P - 2] (mod K) on x and y.
-struct TileCols {
-  int lo[2], n[2];
-};
-__device__ inline TileCols tile_columns(const RepDesc& R, const MeshTile& mt, int P) {
-  TileCols tc;
-  const int t0[2] = {mt.x0, mt.y0};
-  const int nt[2] = {mt.nxy & 0xffff, mt.nxy >> 16};
-#pragma unroll
-  for (int d = 0; d < 2; ++d) {
-    const long long nc = R.nc[d], K = R.K[d];
-    const int lo = (int)((t0[d] * nc) / K);
-    const int hi = (int)(((long long)(t0[d] + nt[d] + P - 1) * nc) / K);
-    if (hi - lo + 1 >= nc) {
-      tc.lo[d] = 0;
-      tc.n[d] = (int)nc;
-    } else {
-      tc.lo[d] = lo;
-      tc.n[d] = hi - lo + 1;
-    }
-  }
-  return tc;
-}
-
 // Start and count of this thread's column of the tile's columns cb.. (zero
 // past the last column).
 struct ColRun {
   int st, n;
 };
 template <int NT>
-__device__ inline ColRun tile_column(const RepDesc& R, const TileCols& tc, const int* __restrict__ qstart, int cb) {
+__device__ inline ColRun tile_column(const RepDesc& R, const MeshTile& mt, const int* __restrict__ qstart, int cb) {
   const int c = cb + threadIdx.x;
   ColRun r{0, 0};
-  if (c < tc.n[0] * tc.n[1]) {
+  if (c < mt.ncol[0] * mt.ncol[1]) {
     const int nx = R.nc[0], ny = R.nc[1], nz = R.nc[2];
-    int cx = tc.lo[0] + c / tc.n[1], cy = tc.lo[1] + c % tc.n[1];
+    const int i = FDiv(mt.ncol[1]).div(c);  // (c < 2^22: at most 1,024 cells per axis)
+    int cx = mt.col0[0] + i, cy = mt.col0[1] + c - i * mt.ncol[1];
     cx -= cx >= nx ? nx : 0;
     cy -= cy >= ny ? ny : 0;
     const int base = R.cell_off + (cx * ny + cy) * nz;
@@ -778,16 +753,16 @@ __device__ inline ColRun tile_column(const RepDesc& R, const TileCols& tc, const
 // its latency overlaps other work.  The order in which beads reach f depends
 // on timing: the callers only add integers.
 template <int NT, typename Keep, typename F>
-__device__ inline void for_tile_beads(const RepDesc& R, const TileCols& tc, const int* __restrict__ qstart,
+__device__ inline void for_tile_beads(const RepDesc& R, const MeshTile& mt, const int* __restrict__ qstart,
                                       ColRun first, int* work, int* s_tot, int* scan_sh, Keep&& keep, F&& f) {
   int* s_cs = work;
   int* s_cp = work + NT;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   int* que = work + 2 * NT + wv * 128;
   int qn = 0;  // wavefront-uniform: queued beads
-  const int ncol = tc.n[0] * tc.n[1];
+  const int ncol = mt.ncol[0] * mt.ncol[1];
   for (int cb = 0; cb < ncol; cb += NT) {
-    const ColRun cr = cb == 0 ? first : tile_column<NT>(R, tc, qstart, cb);
+    const ColRun cr = cb == 0 ? first : tile_column<NT>(R, mt, qstart, cb);
     const int inc = block_scan_incl(cr.n, scan_sh);
     s_cs[threadIdx.x] = cr.st;
     s_cp[threadIdx.x] = inc - cr.n;
@@ -897,8 +872,8 @@ __global__ __launch_bounds__(FFT_THREADS) void k_spread_z(PmeLaunch a) {
   wave_stamp(a.stamps, 0);
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_tot, scan_sh[FFT_THREADS / 64];
-  const MeshTile mt = a.tiles[xcd_item(blockIdx.x, gridDim.x)];
-  const RepDesc& R = a.rep[mt.rep];
+  const MeshTile mt = uniform_load(a.tiles + xcd_item(blockIdx.x, a.ntiles));
+  const RepDesc R = uniform_load(a.rep + mt.rep);
   const int K0 = R.K[0], K1 = R.K[1], K2 = R.K[2], K2h = R.K2h;
   // the tile's real z lines are transformed two to a complex line: line l
   // is the real (l even) or imaginary (l odd) part of packed line l / 2
@@ -910,8 +885,7 @@ __global__ __launch_bounds__(FFT_THREADS) void k_spread_z(PmeLaunch a) {
   // the tile's first column run and this thread's twiddle are loaded first;
   // the twiddles go to LDS after the spread, so neither latency is waited
   // for on its own
-  const TileCols tc = tile_columns(R, mt, P);
-  const ColRun first = tile_column<FFT_THREADS>(R, tc, a.qstart, 0);
+  const ColRun first = tile_column<FFT_THREADS>(R, mt, a.qstart, 0);
   cplx<T>* tw = B + SB;
   const cplx<T>* tws = reinterpret_cast<const cplx<T>*>(a.tw) + R.tw_off[2];
   const cplx<T> tw0 = threadIdx.x < K2 ? tws[threadIdx.x] : cplx<T>{};
@@ -932,7 +906,7 @@ __global__ __launch_bounds__(FFT_THREADS) void k_spread_z(PmeLaunch a) {
     return ox <= nxt + P - 2 && oy <= nyt + P - 2;
   };
   // A is free until the transform: the enumeration's tables go there
-  for_tile_beads<FFT_THREADS>(R, tc, a.qstart, first, reinterpret_cast<int*>(A), &s_tot, scan_sh, keep, [&](int q) {
+  for_tile_beads<FFT_THREADS>(R, mt, a.qstart, first, reinterpret_cast<int*>(A), &s_tot, scan_sh, keep, [&](int q) {
     const uint4 rec = a.qpk[q];
     int k0[3];
     T t[3];
@@ -1048,8 +1022,8 @@ __global__ __launch_bounds__(FFT_THREADS) void k_z_gather(PmeLaunch a) {
   wave_stamp(a.stamps, 0);
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_tot, scan_sh[FFT_THREADS / 64];
-  const MeshTile mt = a.tiles[xcd_item(blockIdx.x, gridDim.x)];
-  const RepDesc& R = a.rep[mt.rep];
+  const MeshTile mt = uniform_load(a.tiles + xcd_item(blockIdx.x, a.ntiles));
+  const RepDesc R = uniform_load(a.rep + mt.rep);
   const int K0 = R.K[0], K1 = R.K[1], K2 = R.K[2], K2h = R.K2h;
   // the tile's real z lines come out of the inverse transform two to a
   // complex line: line l is the real (l even) or imaginary (l odd) part of
@@ -1059,8 +1033,7 @@ __global__ __launch_bounds__(FFT_THREADS) void k_z_gather(PmeLaunch a) {
   const int SB = tile_buf_elems(a.maxK[0], NL, P, (int)sizeof(cplx<T>));
   cplx<T>* A = reinterpret_cast<cplx<T>*>(smem);
   cplx<T>* B = A + SB;
-  const TileCols tc = tile_columns(R, mt, P);
-  const ColRun first = tile_column<FFT_THREADS>(R, tc, a.qstart, 0);
+  const ColRun first = tile_column<FFT_THREADS>(R, mt, a.qstart, 0);
   const cplx<T>* in = reinterpret_cast<const cplx<T>*>(a.Qc) + R.cgrid_off;
   const FDiv dk2h(K2h), dnp(NP), dty(TY);
   // mesh offset of frequency m of tile line l (negative outside the tile)
@@ -1130,7 +1103,7 @@ __global__ __launch_bounds__(FFT_THREADS) void k_z_gather(PmeLaunch a) {
   };
   // the buffer the transform did not end in holds the enumeration's tables
   int* work = reinterpret_cast<int*>(res == A ? B : A);
-  for_tile_beads<FFT_THREADS>(R, tc, a.qstart, first, work, &s_tot, scan_sh, keep, [&](int q) {
+  for_tile_beads<FFT_THREADS>(R, mt, a.qstart, first, work, &s_tot, scan_sh, keep, [&](int q) {
     const uint4 rec = a.qpk[q];
     const int bi = a.qidx[q];
     int k0[3];
