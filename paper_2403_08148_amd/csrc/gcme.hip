@@ -162,7 +162,7 @@ struct gcme_ctx {
   std::vector<double> zz;     // [R][MAXT] sum of z^2 over the beads of each type
   // device buffers
   DevBuf a_pos[3], a_vel[3], a_param, a_id;
-  DevBuf b_pos[3], b_vel[3], b_param, b_id;
+  DevBuf b_pos[3], b_vel, b_param, b_id;  // (b_vel: [3][N], also the records of launch_state_out)
   DevBuf cell, tmp, counts, qcounts, fill, start, qstart, bsum;
   DevBuf b_pk, q_pk, q_idx;
   DevBuf F;
@@ -302,7 +302,16 @@ StateView view(DevBuf* pos, DevBuf* vel, DevBuf& param, DevBuf& id) {
 }
 
 StateView viewA(gcme_handle h) { return view(h->a_pos, h->a_vel, h->a_param, h->a_id); }
-StateView viewB(gcme_handle h) { return view(h->b_pos, h->b_vel, h->b_param, h->b_id); }
+StateView viewB(gcme_handle h) {
+  StateView v;
+  for (int k = 0; k < 3; ++k) {
+    v.pos[k] = h->b_pos[k].as<uint32_t>();
+    v.vel[k] = h->b_vel.as<double>() + (size_t)k * h->N;
+  }
+  v.param = h->b_param.as<uint32_t>();
+  v.id = h->b_id.as<int>();
+  return v;
+}
 
 CellView cview(gcme_handle h) {
   CellView c;
@@ -1558,8 +1567,8 @@ bool alloc_bead_buffers(gcme_handle h, bool derivs) {
     ok &= h->a_pos[k].alloc(N * 4) == hipSuccess;
     ok &= h->b_pos[k].alloc(N * 4) == hipSuccess;
     ok &= h->a_vel[k].alloc(N * 8) == hipSuccess;
-    ok &= h->b_vel[k].alloc(N * 8) == hipSuccess;
   }
+  ok &= h->b_vel.alloc(N * 24) == hipSuccess;
   ok &= h->a_param.alloc(N * 4) == hipSuccess;
   ok &= h->b_param.alloc(N * 4) == hipSuccess;
   ok &= h->a_id.alloc(N * 4) == hipSuccess;
@@ -1906,7 +1915,10 @@ gcme_status gcme_get_state(gcme_handle h, double* pos, double* vel, uint64_t* st
     gcme_status st = build_plan(h);
     if (st != GCME_OK) return st;
   }
-  if (pos || vel) launch_state_out(h->stream, viewA(h), h->d_rep.as<RepDesc>(), pos, vel, h->N, h->N);
+  // (the sorted copy is rebuilt by the next sort: room for the records)
+  if (pos || vel)
+    launch_state_out(h->stream, viewA(h), h->d_rep.as<RepDesc>(), pos, vel, h->b_pk.as<uint4>(), h->b_vel.as<double>(),
+                     h->N);
   HIPCHK(h, hipGetLastError());
   if (step) *step = h->step;
   return GCME_OK;

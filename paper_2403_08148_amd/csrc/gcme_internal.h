@@ -539,8 +539,10 @@ void launch_gather_vjp(hipStream_t s, StateView B, const double* v, double* vs, 
 // dE/da_i from dq plus the self-energy term self_a[rep][type] z_i^2.
 void launch_bead_adj_out(hipStream_t s, StateView B, const double* dg, const double* dq, const double* self_a,
                          double* out_sigma, double* out_a, int N);
-void launch_state_out(hipStream_t s, StateView A, const RepDesc* rep, double* pos, double* vel,
-                      long long ld, int N);
+// Positions and velocities (each may be null) in original order, [3][N]; pr
+// [N] and vr [3 N] are scratch.
+void launch_state_out(hipStream_t s, StateView A, const RepDesc* rep, double* pos, double* vel, uint4* pr, double* vr,
+                      int N);
 constexpr int FIN_VALUES = 8 * (N_SLOTS + 4);  // sums per replica: the slots' and 32 of the adjoint
 struct FinalLaunch {
   const RepDesc* rep;

@@ -240,6 +240,41 @@ __global__ void k_state_out(StateView A, const RepDesc* rep, double* pos, double
   }
 }
 
+// The same in two passes, for large systems: the state's order and the
+// original one are unrelated, so every store of k_state_out is a memory line
+// of its own, six per bead.  First each bead's position and velocity go to its
+// place as one record each (about two lines), then the records are read and
+// the arrays written in order.  N = 2,097,152: 139 us against 208 us in one pass;
+// below a quarter of a million beads one launch is as fast.
+constexpr int STATE_RECORD_BEADS = 262144;
+
+__global__ void k_state_records(StateView A, uint4* pr, double* vr, int N) {
+  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= N) return;
+  const int id = A.id[s];
+  if (pr) pr[id] = make_uint4(A.pos[0][s], A.pos[1][s], A.pos[2][s], A.param[s]);
+  if (vr) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) vr[3 * (size_t)id + k] = A.vel[k][s];
+  }
+}
+
+__global__ void k_state_unpack(const RepDesc* rep, const uint4* pr, const double* vr, double* pos, double* vel, int N) {
+  const int n = blockIdx.x * blockDim.x + threadIdx.x;
+  if (n >= N) return;
+  if (pos) {
+    const uint4 p = pr[n];
+    const RepDesc& R = rep[param_rep(p.w)];
+    pos[n] = (double)p.x * R.scaled[0];
+    pos[(size_t)N + n] = (double)p.y * R.scaled[1];
+    pos[2 * (size_t)N + n] = (double)p.z * R.scaled[2];
+  }
+  if (vel) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) vel[k * (size_t)N + n] = vr[3 * (size_t)n + k];
+  }
+}
+
 // One thread's share of a column of the rows [lo, hi) (W doubles each): rows
 // lo + first, lo + first + step, ..., four loads in flight, in a fixed order.
 template <int W>
@@ -416,9 +451,14 @@ void launch_bead_adj_out(hipStream_t s, StateView B, const double* dg, const dou
   hipLaunchKernelGGL(k_bead_adj_out, dim3(nblk(N, 256)), dim3(256), 0, s, B, dg, dq, self_a, out_sigma, out_a, N);
 }
 
-void launch_state_out(hipStream_t s, StateView A, const RepDesc* rep, double* pos, double* vel, long long ld,
+void launch_state_out(hipStream_t s, StateView A, const RepDesc* rep, double* pos, double* vel, uint4* pr, double* vr,
                       int N) {
-  hipLaunchKernelGGL(k_state_out, dim3(nblk(N, 256)), dim3(256), 0, s, A, rep, pos, vel, ld, N);
+  if (N >= STATE_RECORD_BEADS) {
+    hipLaunchKernelGGL(k_state_records, dim3(nblk(N, 256)), dim3(256), 0, s, A, pos ? pr : nullptr, vel ? vr : nullptr, N);
+    hipLaunchKernelGGL(k_state_unpack, dim3(nblk(N, 256)), dim3(256), 0, s, rep, pr, vr, pos, vel, N);
+    return;
+  }
+  hipLaunchKernelGGL(k_state_out, dim3(nblk(N, 256)), dim3(256), 0, s, A, rep, pos, vel, N, N);
 }
 
 void launch_outputs(hipStream_t s, const OutLaunch& a) {
