@@ -928,15 +928,18 @@ __global__ __launch_bounds__(NL_WAVES * 64) void k_nl_force(PairLaunch a) {
 constexpr int RING = 128;  // pending-pair ring per wavefront (entries)
 static_assert(RING == 128, "the drain relies on a ring of exactly two 64-entry halves");
 
-// Wavefronts per SIMD the list-free kernel is compiled for: the per-step
-// variant (single precision, forces only) is held to 128 VGPRs, so four
-// wavefronts share each SIMD instead of three (it then has no spills: the
-// excluded-volume pairs of N = 2,097,152 took 1.34 -> 1.08 ms, of N = 32,768
-// 48 -> 36 us); the others keep the compiler's choice, since the bound would
-// make them spill.
+// Wavefronts per SIMD the list-free kernel is compiled for, at least: the
+// kernel is bound by instruction issue, and fewer than four wavefronts leave
+// gaps between the LDS reads of a drain and their use.  In single precision
+// forces alone take 82 registers without being told (five wavefronts); left
+// to itself the compiler gave energies 143 and the adjoint 141 (three), and
+// both fit 124 without a spill.  Evaluations of 199,999 beads, three and four
+// wavefronts: energies 428 and 398 us, with the virial 459 and 431, adjoint
+// 620 and 542; of 32,768 beads 143 and 139, 154 and 149, 198 and 176.  Double
+// precision does not fit 128 registers, and counting is no timed path.
 template <typename T, bool EV, bool ADJ, bool COUNT>
 struct FusedWaves {
-  static constexpr int value = std::is_same<T, float>::value && !EV && !ADJ && !COUNT ? 4 : 1;
+  static constexpr int value = std::is_same<T, float>::value && !COUNT ? 4 : 1;
 };
 
 template <typename T, int CI, bool ELEC, bool EV, bool ADJ, bool COUNT>
