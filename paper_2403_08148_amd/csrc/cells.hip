@@ -83,70 +83,81 @@ __device__ inline int block_incl_scan(int v, int* sh) {
   return v + add;
 }
 
-// Exclusive scan of the n cell counts cnt into st (st[n] = the total) and,
-// with fill, a copy of st in fill (the scatter's cursors).  One block of NT
-// threads: the counts pass through buf (n ints of LDS), each thread sums a
-// contiguous chunk, one block scan, then each thread writes its chunk.  The
-// loads of U rounds are issued before any is stored.
-template <int NT, int U>
-__device__ inline void block_scan_counts(const int* cnt, int* st, int* fill, int n, int* buf, int* sh) {
-  for (int i0 = threadIdx.x; i0 < n; i0 += U * NT) {
-    int v[U];
+// The whole scan in one launch, for grids of up to SELF_SCAN_MAX cells: block
+// b of an array (blockIdx.y 0: all beads, 1: charged beads) adds up the counts
+// of all cells before its own itself, four at a time and SELF_SCAN_UNROLL
+// loads in flight, and then scans its own.  Produces start (exclusive) and,
+// for all beads, the scatter cursor fill = start.  It is bound by the latency
+// of a load, a block scan and a store: the one-block scan it replaces took
+// 4.9 us for 32,768 beads (step 80 -> 78 us), and this 3.4.  The counts read
+// twice grow with the square of the grid, which sets the limit: for 96,000
+// beads between walls this takes 5.0 us, and 3.3 + 5.1 and a gap in the two
+// launches below; for 256 replicas (above the limit) 12.2, and 4.6 + 5.1; for
+// N = 2,097,152 49, and about 20.
+constexpr int SELF_SCAN_THREADS = 1024;
+constexpr int SELF_SCAN_BLOCK = 4 * SELF_SCAN_THREADS;
+constexpr int SELF_SCAN_UNROLL = 8;
+constexpr int SELF_SCAN_MAX = 131072;
+
+__global__ __launch_bounds__(SELF_SCAN_THREADS) void k_scan_self(CellView c) {
+  constexpr int NT = SELF_SCAN_THREADS, NW = NT / 64, U = SELF_SCAN_UNROLL;
+  __shared__ int s_own[NW], s_off[NW];
+  const int n = c.ncells;
+  const int* __restrict__ cnt = blockIdx.y == 0 ? c.counts : c.qcounts;
+  int* __restrict__ st = blockIdx.y == 0 ? c.start : c.qstart;
+  if (c.step && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *c.step += 1ULL;
+  const int base = blockIdx.x * SELF_SCAN_BLOCK + threadIdx.x * 4;
+  int v[4];
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = i0 + u * NT < n ? cnt[i0 + u * NT] : 0;
+  for (int u = 0; u < 4; ++u) v[u] = base + u < n ? cnt[base + u] : 0;
+  // (the blocks before this one are whole)
+  const int4* __restrict__ cnt4 = reinterpret_cast<const int4*>(cnt);
+  const int nb4 = blockIdx.x * NT;
+  int off = 0;
+  for (int i0 = threadIdx.x; i0 < nb4; i0 += U * NT) {
+    int4 w[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (i0 + u * NT < n) buf[i0 + u * NT] = v[u];
+    for (int u = 0; u < U; ++u) w[u] = i0 + u * NT < nb4 ? cnt4[i0 + u * NT] : make_int4(0, 0, 0, 0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) off += (w[u].x + w[u].y) + (w[u].z + w[u].w);
+  }
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int own = (v[0] + v[1]) + (v[2] + v[3]);
+  int inc = own;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(inc, o, 64);
+    off += __shfl_xor(off, o, 64);
+    if (lane >= o) inc += t;
+  }
+  if (lane == 63) {
+    s_own[wid] = inc;
+    s_off[wid] = off;
   }
   __syncthreads();
-  const int per = (n + NT - 1) / NT;
-  const int lo = threadIdx.x * per, hi = min(lo + per, n);
-  int s = 0;
-  for (int i = lo; i < hi; i += 4) {
-    int v[4];
+  int run = inc - own;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = i + u < hi ? buf[i + u] : 0;
-    s += (v[0] + v[1]) + (v[2] + v[3]);
-  }
-  const int inc = block_incl_scan<NT>(s, sh);
-  int run = inc - s;
-  for (int i = lo; i < hi; i += 4) {
-    int v[4];
+  for (int w = 0; w < NW; ++w) run += s_off[w] + (w < wid ? s_own[w] : 0);
+  int r[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = i + u < hi ? buf[i + u] : 0;
+  for (int u = 0; u < 4; ++u) {
+    r[u] = run;
+    run += v[u];
+  }
+  if (base + 4 <= n) {
+    const int4 o = make_int4(r[0], r[1], r[2], r[3]);
+    *reinterpret_cast<int4*>(st + base) = o;
+    if (blockIdx.y == 0) *reinterpret_cast<int4*>(c.fill + base) = o;
+  } else {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (i + u < hi) buf[i + u] = run;
-      run += v[u];
-    }
+    for (int u = 0; u < 4; ++u)
+      if (base + u < n) {
+        st[base + u] = r[u];
+        if (blockIdx.y == 0) c.fill[base + u] = r[u];
+      }
   }
-  if (threadIdx.x == NT - 1) st[n] = inc;
-  __syncthreads();
-  for (int i = threadIdx.x; i < n; i += NT) {
-    const int v = buf[i];
-    st[i] = v;
-    if (fill) fill[i] = v;
-  }
-  __syncthreads();  // buf may be reused at once
-}
-
-// Whole scan in one block per array (block 0: all beads, block 1: charged
-// beads) for grids of up to SINGLE_SCAN_MAX cells: each thread sums a
-// contiguous chunk, one block scan, then each thread writes its chunk.
-// Produces start (exclusive) and, for all beads, the scatter cursor
-// fill = start.
-constexpr int SINGLE_SCAN_THREADS = 1024;
-constexpr int SCAN_UNROLL = 16;
-constexpr int SINGLE_SCAN_MAX = 38912;  // counts staged in up to 152 KiB of LDS
-
-__global__ __launch_bounds__(SINGLE_SCAN_THREADS) void k_scan_single(CellView c) {
-  __shared__ int sh[SINGLE_SCAN_THREADS / 64];
-  extern __shared__ __align__(16) int buf[];  // ncells entries
-  if (c.step && blockIdx.x == 0 && threadIdx.x == 0) *c.step += 1ULL;
-  if (blockIdx.x == 0)
-    block_scan_counts<SINGLE_SCAN_THREADS, SCAN_UNROLL>(c.counts, c.start, c.fill, c.ncells, buf, sh);
-  else
-    block_scan_counts<SINGLE_SCAN_THREADS, SCAN_UNROLL>(c.qcounts, c.qstart, nullptr, c.ncells, buf, sh);
+  // (run of the last thread: the total)
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == NT - 1) st[n] = run;
 }
 
 __global__ void k_scan_reduce(CellView c, int nb) {
@@ -539,10 +550,8 @@ void launch_bin(hipStream_t s, StateView A, const RepDesc* rep, CellView c, long
 }
 
 static void launch_scan(hipStream_t s, CellView c) {
-  if (c.ncells <= SINGLE_SCAN_MAX) {
-    const size_t sh = (size_t)c.ncells * 4;
-    if (sh > 65536) (void)hipFuncSetAttribute((const void*)k_scan_single, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-    hipLaunchKernelGGL(k_scan_single, dim3(2), dim3(SINGLE_SCAN_THREADS), sh, s, c);
+  if (c.ncells <= SELF_SCAN_MAX) {
+    hipLaunchKernelGGL(k_scan_self, dim3(nblk(c.ncells, SELF_SCAN_BLOCK), 2), dim3(SELF_SCAN_THREADS), 0, s, c);
     return;
   }
   int nb = nblk(c.ncells, SCAN_BLOCK);

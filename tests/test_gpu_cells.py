@@ -49,3 +49,26 @@ def test_cells_against_oracle(case, n, direct):
                 err = rel_rms(out["force"].t().cpu().numpy(), ref["F"])
                 assert err < TOL[prec], (case, n, prec, ci, ev, err)
             eng.close()
+
+
+# cells of the grid (rc = 1, one cell per cutoff across, two along z): the
+# scan's blocks of 4,096 cells and the cells beside them, and both sides of
+# 131,072, where the one-launch scan ends; more beads than the one-block sort
+# takes.  FP64, TOL as above.
+GRIDS = {4095: (15, 13, 21), 4096: (16, 16, 16), 4100: (10, 10, 41), 8192: (16, 16, 32),
+         131040: (63, 65, 32), 131072: (64, 64, 32), 133120: (65, 64, 32)}
+
+
+@pytest.mark.parametrize("cells", sorted(GRIDS))
+def test_scan_sizes_against_oracle(cells):
+    nx, ny, nz = GRIDS[cells]
+    assert nx * ny * nz == cells
+    w = W.small_bulk(N=4203, seed=7, box=(nx + 0.2, ny + 0.2, (nz + 0.4) / 2), rc=1.0, grid=(64, 64, 32))
+    ref = oracle_eval(w)
+    eng = make_engine([w], "fp64", tuning=dict(cells_per_cutoff=1, direct_pairs=3))
+    for _ in range(2):  # again from the counts that the first sort left cleared
+        out = eng.forces_energy(energy=False, virial=False)
+        eng.sync()
+        err = rel_rms(out["force"].t().cpu().numpy(), ref["F"])
+        assert err < TOL["fp64"], (cells, err)
+    eng.close()
