@@ -329,7 +329,9 @@ gcme_status gcme_forces_energy_noalloc(const gcme_params* p, int32_t n_beads, in
  * consecutive cell-sorted beads, either with one neighbour list per cluster
  * (built each evaluation) or list-free (each cluster evaluates the beads of
  * its cell columns directly).  Both visit the same pairs with the same
- * cutoff test; they differ in the order of the per-bead sums. */
+ * cutoff test; they differ in the order of the per-bead sums.  While no
+ * cluster size has been given, the list-free pairs of a small system take
+ * smaller clusters than the default that gcme_get_tuning reports. */
 typedef struct {
     int32_t cells_per_cutoff;    /* cells of about (rc / n)^3, flat along z (1..4) */
     int32_t beads_per_cluster;   /* excluded-volume cluster size (2, 4, 8) */

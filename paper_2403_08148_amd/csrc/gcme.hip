@@ -157,6 +157,8 @@ struct gcme_ctx {
   // 84 / 104 and 106 / 111; the adsorption study's slabs 845 / 916 and 743 / 786
   // for four; N = 2,097,152 alike)
   gcme_tuning tune{3, 8, 4, 50, 3, 2, 0, 0, 0, 0, 0};
+  bool ci_given[2] = {false, false};  // a caller (or the autotuner) chose the cluster sizes: beads, charges
+  int ci[2] = {8, 4};                 // ... and those of the plan
   bool plan_dirty = true;
   bool tables_dirty = false;  // only the pair strengths and radii have changed since the plan
   std::vector<double> zz;     // [R][MAXT] sum of z^2 over the beads of each type
@@ -559,6 +561,33 @@ void build_mesh_tables(gcme_handle h, std::vector<T>& tw, std::vector<T>& bsp, s
   }
 }
 
+// The column-cluster mode of the excluded-volume (charged) pairs:
+// 0 = cluster kernels, 1 = half shell, 2 = both ends (tuning half_pairs).
+int col_mode(gcme_handle h, bool charged) { return (h->tune.half_pairs >> (charged ? 2 : 0)) & 3; }
+
+// The cluster size of the excluded-volume (charged) pairs: what the tuning
+// gives, or, where no caller has given one and the pairs are list-free, the
+// smallest that still gives every wavefront (one cluster each) room on the
+// chip's 1,024 SIMDs at once: three clusters of 2 or four of 4 beads a SIMD,
+// and four of 2 charges.  A large cluster shares the search for its partners
+// among more beads, which is the lesser cost once the chip is full; before
+// that the length of one cluster's work is the stage's time.  Excluded volume
+// with clusters of 8, 4 and 2, single precision: 1,536 beads 20, 15 and 14
+// us, 6,144 19, 16 and 15, 16,384 21, 19 and 26, 24,000 23, 26 and 34; charged
+// pairs: 6,554 charges among 32,768 beads 17, 11 and 9, 8,192 charges 33, 24
+// and 21, 12,288 28, 19 and 21.  In double precision the lines lie at or above
+// these.
+int cluster_size(gcme_handle h, bool charged) {
+  const int ci = charged ? h->tune.charges_per_cluster : h->tune.beads_per_cluster;
+  if (h->ci_given[charged] || !((h->tune.direct_pairs >> (charged ? 1 : 0)) & 1) || col_mode(h, charged))
+    return ci;
+  constexpr long long SIMDS = 1024;
+  const long long n = charged ? h->NQ : h->N;
+  if (n <= 2 * (charged ? 4 : 3) * SIMDS) return std::min(ci, 2);
+  if (n <= 4 * 4 * SIMDS) return std::min(ci, 4);
+  return ci;
+}
+
 // Clusters of `ci` consecutive beads of each replica's sorted population
 // (all beads, or the compacted charged beads), tiled in groups of
 // pair_waves_per_block() clusters of one replica (one pair-kernel workgroup
@@ -604,10 +633,6 @@ void plan_clusters(gcme_handle h, bool charged, int ci, std::vector<int2>& cl, s
   toff[h->R] = (int)tiles.size();
   cap = ((int)std::ceil(cmax) + 63) & ~63;
 }
-
-// The column-cluster mode of the excluded-volume (charged) pairs:
-// 0 = cluster kernels, 1 = half shell, 2 = both ends (tuning half_pairs).
-int col_mode(gcme_handle h, bool charged) { return (h->tune.half_pairs >> (charged ? 2 : 0)) & 3; }
 
 gcme_status build_plan(gcme_handle h) {
   hipStream_t s = h->stream;
@@ -864,8 +889,10 @@ gcme_status build_plan(gcme_handle h) {
   std::vector<int> toff_g, toff_q, toff_256;
   std::vector<int2> clg, clq;
   std::vector<Tile> tg, tq;
-  plan_clusters(h, false, h->tune.beads_per_cluster, clg, tg, toff_g, h->cap_g);
-  plan_clusters(h, true, h->tune.charges_per_cluster, clq, tq, toff_q, h->cap_q);
+  h->ci[0] = cluster_size(h, false);
+  h->ci[1] = cluster_size(h, true);
+  plan_clusters(h, false, h->ci[0], clg, tg, toff_g, h->cap_g);
+  plan_clusters(h, true, h->ci[1], clq, tq, toff_q, h->cap_q);
   std::vector<Tile> t256 = make_tiles(h->boff, h->nb, 256, toff_256);
   h->ncl_g = (int)clg.size();
   h->ncl_q = (int)clq.size();
@@ -1068,7 +1095,7 @@ PairLaunch pair_args(gcme_handle h, bool charged) {
     a.ntiles = h->ntiles_q;
     a.cl = h->d_cl_q.as<int2>();
     a.ncl = h->ncl_q;
-    a.ci = h->tune.charges_per_cluster;
+    a.ci = h->ci[1];
     a.direct = (h->tune.direct_pairs >> 1) & 1;
     a.cap = h->cap_q;
     a.list = h->list_q.as<uint32_t>();
@@ -1086,7 +1113,7 @@ PairLaunch pair_args(gcme_handle h, bool charged) {
     a.ntiles = h->ntiles_g;
     a.cl = h->d_cl_g.as<int2>();
     a.ncl = h->ncl_g;
-    a.ci = h->tune.beads_per_cluster;
+    a.ci = h->ci[0];
     a.direct = h->tune.direct_pairs & 1;
     a.cap = h->cap_g;
     a.list = h->list_g.as<uint32_t>();
@@ -1978,51 +2005,59 @@ gcme_status gcme_forces_energy_noalloc(const gcme_params* p, int32_t n_beads, in
   gcme_status st = scratch_address(dev, &base);
   if (st != GCME_OK) return st;
   // a transient context on the caller's stream: no streams, events or
-  // graphs of its own, every device buffer carved from the scratch
-  gcme_handle h = new gcme_ctx();
-  h->device = dev;
-  h->stream = (hipStream_t)stream;
-  h->R = 1;
-  h->nb.assign(1, n_beads);
-  h->boff.assign(1, 0);
-  h->N = n_beads;
-  h->fp64 = precision == GCME_FP64;
-  {
-    int lds = 0;
-    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && lds > 0)
-      h->lds_max = lds - 4096;
-  }
-  h->hp.assign(1, HostRep{});
-  h->bonds.assign(1, {});
-  h->nq.assign(1, 0);
-  h->qoff.assign(1, 0);
+  // graphs of its own, every device buffer carved from the scratch.  A system
+  // that does not fit with the smaller clusters of cluster_size is planned
+  // again with the tuning's own, which take fewer partial sums (no kernel has
+  // run by then).
   Arena arena;
-  arena.base = (char*)base;
-  arena.size = GCME_NOALLOC_SCRATCH_BYTES;
-  t_arena = &arena;
-  if (!alloc_bead_buffers(h, false)) {
-    st = GCME_ENOMEM;
-    h->err = "device buffers";
+  for (const bool tuning_sizes : {false, true}) {
+    gcme_handle h = new gcme_ctx();
+    h->device = dev;
+    h->stream = (hipStream_t)stream;
+    h->R = 1;
+    h->nb.assign(1, n_beads);
+    h->boff.assign(1, 0);
+    h->N = n_beads;
+    h->fp64 = precision == GCME_FP64;
+    h->ci_given[0] = h->ci_given[1] = tuning_sizes;
+    {
+      int lds = 0;
+      if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && lds > 0)
+        h->lds_max = lds - 4096;
+    }
+    h->hp.assign(1, HostRep{});
+    h->bonds.assign(1, {});
+    h->nq.assign(1, 0);
+    h->qoff.assign(1, 0);
+    arena = Arena{};
+    arena.base = (char*)base;
+    arena.size = GCME_NOALLOC_SCRATCH_BYTES;
+    t_arena = &arena;
+    st = GCME_OK;
+    if (!alloc_bead_buffers(h, false)) {
+      st = GCME_ENOMEM;
+      h->err = "device buffers";
+    }
+    if (st == GCME_OK) st = gcme_set_params(h, -1, p);
+    if (st == GCME_OK) st = gcme_set_state(h, pos, nullptr, type, z);
+    if (st == GCME_OK) {
+      gcme_io io{};
+      io.force = force;
+      io.energy = energy;
+      io.virial = virial;
+      st = gcme_forces_energy(h, &io);
+    }
+    if (st == GCME_OK) st = gcme_sync(h);
+    t_arena = nullptr;
+    const bool smaller = h->ci[0] != h->tune.beads_per_cluster || h->ci[1] != h->tune.charges_per_cluster;
+    if (st != GCME_OK) g_create_err = h->err;
+    delete h;
+    if (!(st == GCME_ENOMEM && arena.need > 0 && smaller)) break;
   }
-  if (st == GCME_OK) st = gcme_set_params(h, -1, p);
-  if (st == GCME_OK) st = gcme_set_state(h, pos, nullptr, type, z);
-  if (st == GCME_OK) {
-    gcme_io io{};
-    io.force = force;
-    io.energy = energy;
-    io.virial = virial;
-    st = gcme_forces_energy(h, &io);
-  }
-  if (st == GCME_OK) st = gcme_sync(h);
-  t_arena = nullptr;
-  if (st == GCME_ENOMEM && arena.need > 0) {
+  if (st == GCME_ENOMEM && arena.need > 0)
     g_create_err = "the evaluation needs " + std::to_string(arena.need) + " bytes of device scratch, more than the " +
                    std::to_string((size_t)GCME_NOALLOC_SCRATCH_BYTES) +
                    " of the no-alloc entry point (use a context from gcme_create)";
-  } else if (st != GCME_OK) {
-    g_create_err = h->err;
-  }
-  delete h;
   return st;
 }
 
@@ -2154,6 +2189,12 @@ gcme_status gcme_set_tuning(gcme_handle h, const gcme_tuning* t) {
       n.mesh_tile_y != h->tune.mesh_tile_y || n.gather_tile_x != h->tune.gather_tile_x ||
       n.gather_tile_y != h->tune.gather_tile_y || n.half_pairs != h->tune.half_pairs) {
     h->tune = n;
+    h->plan_dirty = true;
+    h->drop_graphs();
+  }
+  if (t->beads_per_cluster >= 0) h->ci_given[0] = true;
+  if (t->charges_per_cluster >= 0) h->ci_given[1] = true;
+  if (!h->plan_dirty && (cluster_size(h, false) != h->ci[0] || cluster_size(h, true) != h->ci[1])) {
     h->plan_dirty = true;
     h->drop_graphs();
   }

@@ -72,3 +72,45 @@ def test_scan_sizes_against_oracle(cells):
         err = rel_rms(out["force"].t().cpu().numpy(), ref["F"])
         assert err < TOL["fp64"], (cells, err)
     eng.close()
+
+
+# Cluster sizes by the number of beads (charged fraction f): up to 6,144 beads
+# clusters of 2, up to 16,384 of 4, above of 8; up to 8,192 charges of 2, above
+# of 4.  Bit-identical to the same sizes given, and the general sizes agree to
+# FP64 sums (TOL).
+SIZES = [(6144, 0.2, 2, 2), (6145, 0.2, 4, 2), (16384, 0.5, 4, 2), (16384, 0.51, 4, 4), (16385, 0.2, 8, 2)]
+
+
+@pytest.mark.parametrize("n,frac,cg,cq", SIZES)
+def test_default_cluster_sizes(n, frac, cg, cq):
+    box = (n / 2.5) ** (1.0 / 3.0)
+    w = W.small_bulk(N=n, seed=8, charged_frac=frac, box=(box, 1.01 * box, 0.99 * box), rc=2.0, grid=(36, 36, 36))
+    F = []
+    for tuning in (None, dict(beads_per_cluster=cg, charges_per_cluster=cq),
+                   dict(beads_per_cluster=8, charges_per_cluster=4)):
+        eng = make_engine([w], "fp64", tuning=tuning)
+        out = eng.forces_energy(energy=True, virial=True)
+        eng.sync()
+        F.append(out["force"].cpu().numpy())
+        eng.close()
+    np.testing.assert_array_equal(F[0], F[1])
+    assert rel_rms(F[0], F[2]) < TOL["fp64"]
+
+
+def test_given_cluster_sizes_stand():
+    """A size once given is kept, also where it is the one that was reported."""
+    w = W.small_bulk(N=700, seed=9, box=(6.6, 6.5, 6.7), rc=2.4, grid=(24, 24, 24))
+    eng = make_engine([w], "mixed")
+    auto = eng.forces_energy()["force"].clone()
+    t = eng.tuning()
+    eng.set_tuning(beads_per_cluster=t["beads_per_cluster"], charges_per_cluster=t["charges_per_cluster"])
+    given = eng.forces_energy()["force"].clone()
+    eng.sync()
+    eng.close()
+    fresh = make_engine([w], "mixed", tuning=dict(beads_per_cluster=8, charges_per_cluster=4))
+    ref = fresh.forces_energy()["force"]
+    fresh.sync()
+    assert t["beads_per_cluster"] == 8 and t["charges_per_cluster"] == 4
+    np.testing.assert_array_equal(given.cpu().numpy(), ref.cpu().numpy())
+    assert rel_rms(auto.cpu().numpy(), ref.cpu().numpy()) < TOL["mixed"]
+    fresh.close()
