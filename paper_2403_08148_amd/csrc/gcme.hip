@@ -195,7 +195,7 @@ struct gcme_ctx {
   T* ptab(int k) const {
     return reinterpret_cast<T*>(d_ptab.as<char>() + pt_off[k]);
   }
-  // k_finalize: blocks per replica, their sums and finished counts
+  // final sums: blocks per replica, their sums and finished counts
   int fin_nb = 1;
   DevBuf fin_part, fin_count;
   // per-bead radius derivatives (sorted order)
