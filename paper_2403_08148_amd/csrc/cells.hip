@@ -83,7 +83,8 @@ __device__ inline int block_incl_scan(int v, int* sh) {
   return v + add;
 }
 
-// The whole scan in one launch, for grids of up to SELF_SCAN_MAX cells: block
+// The whole scan in one launch, for grids of up to SELF_SCAN_MAX cells (those
+// that no bucket sort takes: larger ones, or with images): block
 // b of an array (blockIdx.y 0: all beads, 1: charged beads) adds up the counts
 // of all cells before its own itself, four at a time and SELF_SCAN_UNROLL
 // loads in flight, and then scans its own.  Produces start (exclusive) and,
@@ -446,6 +447,212 @@ __global__ __launch_bounds__(SMALL_SORT_THREADS) void k_sort_small(StateView A, 
   }
 }
 
+// The whole sort in one launch from the buckets that the binning filled, for
+// grids of up to BUCKET_SORT_CELLS cells.  A block takes `per` consecutive
+// cells: it adds up the counts of the cells before them itself (as
+// k_scan_self), scans its own, and moves their beads: 16 lanes, a DPP row,
+// hold the entries of a cell, whose ranks (beads of the cell with a smaller
+// previous index) are 15 row rotations.  The counts are cleared for the next
+// binning by the last block to have read them.  The beads of a cell of more
+// than CELL_CAP are ranked in LDS, from its bucket and the list of those that
+// found one full; a block with more than BUCKET_LIST of them lets one
+// wavefront meet them in order by going through all N (neither in a fluid of
+// some three beads a cell).
+// It is bound by latency: the load of the counts, a block scan, then the loads
+// and stores of a bead.  Against scan, scatter and permute, the whole sort and
+// its gaps: 4,099 beads 13.0 -> 10.0 us, 32,768 15.5 -> 13.0 (ten steps 787 ->
+// 746 us); steps of 8,000 beads 56 -> 51, 16,384 61 -> 56, 50,000 (18,000
+// cells) 84.6 -> 82, and no gain at 80,000 (29,000 cells) and above, since
+// every block reads all counts before its own.
+constexpr int BUCKET_SORT_THREADS = 1024;
+constexpr int BUCKET_SORT_CELLS = 24576;
+constexpr int BUCKET_LIST = 2048;
+constexpr int BUCKET_PER_MAX = 1024;
+static_assert(CELL_CAP == 16, "a cell's bucket is one DPP row");
+
+template <int R>
+__device__ inline void row_ranks(uint32_t key, int& rank, int& qrank) {
+  if constexpr (R < 16) {
+    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0x120 + R, 0xf, 0xf, false);  // row_ror:R
+    rank += o < key;
+    qrank += o < key && (o & 1u);
+    row_ranks<R + 1>(key, rank, qrank);
+  }
+}
+
+__device__ inline void move_bead(const StateView& A, const StateView& B, uint4* __restrict__ bpk, const CellView& c,
+                                 const ChargedView& q, int N, int s, int n, int qn) {
+  // (inconsistent counts cannot send an access out of bounds)
+  if ((unsigned)s >= (unsigned)N || (unsigned)n >= (unsigned)N) return;
+  const uint32_t prm = A.param[s];
+  const uint32_t px = A.pos[0][s], py = A.pos[1][s], pz = A.pos[2][s];
+  const double vx = A.vel[0][s], vy = A.vel[1][s], vz = A.vel[2][s];
+  const int id = A.id[s];
+  B.pos[0][n] = px;
+  B.pos[1][n] = py;
+  B.pos[2][n] = pz;
+  B.vel[0][n] = vx;
+  B.vel[1][n] = vy;
+  B.vel[2][n] = vz;
+  B.param[n] = prm;
+  B.id[n] = id;
+  if (c.slot_of && (unsigned)id < (unsigned)N) c.slot_of[id] = n;
+  const uint4 rec = make_uint4(px, py, pz, prm);
+  bpk[n] = rec;
+  if (param_z(prm) != 0 && (unsigned)qn < (unsigned)q.n) {
+    q.pk[qn] = rec;
+    q.idx[qn] = n;
+  }
+}
+
+__global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_sort_buckets(StateView A, StateView B, uint4* __restrict__ bpk,
+                                                                      CellView c, ChargedView q, int N, int per) {
+  constexpr int NT = BUCKET_SORT_THREADS, NW = NT / 64, U = 4;
+  __shared__ int s_own[2][NW], s_off[2][NW];
+  __shared__ int s_cnt[BUCKET_PER_MAX], s_start[BUCKET_PER_MAX], s_qstart[BUCKET_PER_MAX];
+  __shared__ uint2 s_list[BUCKET_LIST];
+  __shared__ int s_over, s_last, s_nlist;
+  const int n = c.ncells, c0 = blockIdx.x * per;
+  const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+  if (c.step && blockIdx.x == 0 && t == 0) *c.step += 1ULL;
+  if (t == 0) s_over = s_nlist = 0;
+  // 1. the starts of this block's cells (c0 is a multiple of 64)
+  const bool mine = t < per && c0 + t < n;
+  const int v0 = mine ? c.counts[c0 + t] : 0, v1 = mine ? c.qcounts[c0 + t] : 0;
+  const int4* __restrict__ k0 = reinterpret_cast<const int4*>(c.counts);
+  const int4* __restrict__ k1 = reinterpret_cast<const int4*>(c.qcounts);
+  int o0 = 0, o1 = 0;
+  for (int i0 = t; i0 < c0 / 4; i0 += U * NT) {
+    int4 a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = i0 + u * NT < c0 / 4;
+      a[u] = in ? k0[i0 + u * NT] : make_int4(0, 0, 0, 0);
+      b[u] = in ? k1[i0 + u * NT] : make_int4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      o0 += (a[u].x + a[u].y) + (a[u].z + a[u].w);
+      o1 += (b[u].x + b[u].y) + (b[u].z + b[u].w);
+    }
+  }
+  int i0 = v0, i1 = v1;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int a = __shfl_up(i0, o, 64), b = __shfl_up(i1, o, 64);
+    o0 += __shfl_xor(o0, o, 64);
+    o1 += __shfl_xor(o1, o, 64);
+    if (lane >= o) {
+      i0 += a;
+      i1 += b;
+    }
+  }
+  if (lane == 63) {
+    s_own[0][wid] = i0;
+    s_own[1][wid] = i1;
+    s_off[0][wid] = o0;
+    s_off[1][wid] = o1;
+  }
+  __syncthreads();  // (every thread's loads of the counts have returned)
+  int tick = 0;
+  if (t == NT - 64) tick = atomicAdd(&c.sortn[0], 1);
+  int r0 = i0 - v0, r1 = i1 - v1;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    r0 += s_off[0][w] + (w < wid ? s_own[0][w] : 0);
+    r1 += s_off[1][w] + (w < wid ? s_own[1][w] : 0);
+  }
+  if (t < per) {
+    s_cnt[t] = v0;
+    s_start[t] = r0;
+    s_qstart[t] = r1;
+    if (mine) {
+      c.start[c0 + t] = r0;
+      c.qstart[c0 + t] = r1;
+      if (c0 + t == n - 1) {
+        c.start[n] = r0 + v0;
+        c.qstart[n] = r1 + v1;
+      }
+    }
+    if (v0 > CELL_CAP) s_over = 1;
+  }
+  __syncthreads();
+  // 2. the beads of the cells that their buckets hold
+  for (int g = t >> 4; g < per; g += NT / 16) {
+    const int cnt = s_cnt[g];
+    if (!__any(cnt > 0)) continue;
+    const bool on = cnt <= CELL_CAP && (t & 15) < cnt;
+    const uint32_t key = on ? c.bucket[(size_t)(c0 + g) * CELL_CAP + (t & 15)] : 0xffffffffu;
+    int rank = 0, qrank = 0;
+    row_ranks<1>(key, rank, qrank);
+    if (on) move_bead(A, B, bpk, c, q, N, (int)(key >> 1), s_start[g] + rank, s_qstart[g] + qrank);
+  }
+  // 3. the others
+  if (s_over) {
+    auto push = [&](uint32_t g, uint32_t key) {
+      const int at = atomicAdd(&s_nlist, 1);
+      if (at < BUCKET_LIST) s_list[at] = make_uint2(g, key);
+    };
+    for (int g = t >> 4; g < per; g += NT / 16)
+      if (s_cnt[g] > CELL_CAP) push((uint32_t)g, c.bucket[(size_t)(c0 + g) * CELL_CAP + (t & 15)]);
+    const int no = min(c.sortn[1], N);
+    for (int i = t; i < no; i += NT) {
+      const uint2 e = c.over[i];
+      if (e.x - (uint32_t)c0 < (uint32_t)per) push(e.x - (uint32_t)c0, e.y);
+    }
+    __syncthreads();
+    const int nl = s_nlist;
+    if (nl <= BUCKET_LIST)
+      for (int i = t; i < nl; i += NT) {
+        const uint2 e = s_list[i];
+        int rank = 0, qrank = 0;
+        for (int k = 0; k < nl; ++k) {
+          const uint2 o = s_list[k];
+          const bool before = o.x == e.x && o.y < e.y;
+          rank += before;
+          qrank += before && (o.y & 1u);
+        }
+        move_bead(A, B, bpk, c, q, N, (int)(e.y >> 1), s_start[e.x] + rank, s_qstart[e.x] + qrank);
+      }
+  }
+  if (s_over && s_nlist > BUCKET_LIST && wid == 0) {
+    for (int b0 = 0; b0 < N; b0 += 64 * U) {
+      int cid[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) cid[u] = b0 + 64 * u + lane < N ? c.cell[b0 + 64 * u + lane] - c0 : -1;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int s = b0 + 64 * u + lane, g = cid[u];
+        const bool m = (unsigned)g < (unsigned)per && s_cnt[g] > CELL_CAP;
+        unsigned long long left = __ballot(m);
+        while (left) {
+          const int gg = __builtin_amdgcn_readlane(g, __ffsll((long long)left) - 1);
+          const bool take = m && g == gg;
+          const bool charged = take && param_z(A.param[s]) != 0;
+          const unsigned long long mm = __ballot(take), mq = __ballot(charged);
+          const unsigned long long below = (1ull << lane) - 1ull;
+          const int base = s_start[gg], qbase = s_qstart[gg];
+          if (take) move_bead(A, B, bpk, c, q, N, s, base + __popcll(mm & below), qbase + __popcll(mq & below));
+          __builtin_amdgcn_wave_barrier();
+          if (lane == 0) {
+            s_start[gg] = base + __popcll(mm);
+            s_qstart[gg] = qbase + __popcll(mq);
+          }
+          __builtin_amdgcn_wave_barrier();
+          left &= ~mm;
+        }
+      }
+    }
+  }
+  // 4. the counts, when every block has read them
+  if (t == NT - 64) s_last = tick == (int)gridDim.x - 1;
+  __syncthreads();
+  if (s_last) {
+    for (int i = t; i < n; i += NT) c.counts[i] = c.qcounts[i] = 0;
+    if (t < 2) c.sortn[t] = 0;
+  }
+}
+
 // Column clusters (see ColLaunch).  One block: the columns' cluster counts
 // are staged in LDS (loads spread over the block), each thread then takes a
 // contiguous run of columns, and a block scan of the runs' counts gives every
@@ -564,11 +771,26 @@ static void launch_scan(hipStream_t s, CellView c) {
   hipLaunchKernelGGL(k_scan_apply<false>, dim3(nb), dim3(SCAN_THREADS), 0, s, c, nb);
 }
 
+bool small_sort(int N, int ncells) { return N <= SMALL_SORT_BEADS && ncells <= SMALL_SORT_CELLS; }
+
+// Buckets pay while the counts are few enough to be summed by every block and
+// a cell's bucket (64 B) holds its beads: of up to seven beads a cell on
+// average, one cell in 3,000 of an ideal gas has more than CELL_CAP.
+bool bucket_sort(int N, int ncells) {
+  return !small_sort(N, ncells) && ncells <= BUCKET_SORT_CELLS && N <= 7LL * ncells;
+}
+
 void launch_sort(hipStream_t s, StateView A, StateView B, uint4* bpk, CellView c, ChargedView q, int N) {
-  if (N <= SMALL_SORT_BEADS && c.ncells <= SMALL_SORT_CELLS) {
+  if (small_sort(N, c.ncells)) {
     const size_t sh = ((size_t)c.ncells + N) * 4;
     if (sh > 65536) (void)hipFuncSetAttribute((const void*)k_sort_small, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
     hipLaunchKernelGGL(k_sort_small, dim3(1), dim3(SMALL_SORT_THREADS), sh, s, A, B, bpk, c, q, N);
+    return;
+  }
+  if (c.bucket) {
+    // about a block per CU, of whole groups of 64 cells
+    const int per = std::max(64, ((c.ncells + 255) / 256 + 63) & ~63);
+    hipLaunchKernelGGL(k_sort_buckets, dim3(nblk(c.ncells, per)), dim3(BUCKET_SORT_THREADS), 0, s, A, B, bpk, c, q, N, per);
     return;
   }
   launch_scan(s, c);

@@ -166,6 +166,8 @@ struct gcme_ctx {
   DevBuf a_pos[3], a_vel[3], a_param, a_id;
   DevBuf b_pos[3], b_vel, b_param, b_id;  // (b_vel: [3][N], also the records of launch_state_out)
   DevBuf cell, tmp, counts, qcounts, fill, start, qstart, bsum;
+  DevBuf bucket, over, sortn;  // one-launch sort from buckets (buckets: in use by this plan)
+  bool buckets = false;
   DevBuf b_pk, q_pk, q_idx;
   DevBuf F;
   DevBuf Qc, d_mtiles, d_gtiles;
@@ -328,6 +330,10 @@ CellView cview(gcme_handle h) {
   c.step = nullptr;
   c.slot_of = h->nbonds > 0 ? h->slot_of.as<int>() : nullptr;
   c.slot_a = h->nimages > 0 ? h->slot_a.as<int>() : nullptr;
+  // (images change cells after the binning)
+  c.bucket = h->buckets && h->nimages == 0 ? h->bucket.as<uint32_t>() : nullptr;
+  c.over = h->over.as<uint2>();
+  c.sortn = h->sortn.as<int>();
   c.ncells = h->ncells;
   return c;
 }
@@ -1046,6 +1052,14 @@ gcme_status build_plan(gcme_handle h) {
   HIPCHK(h, h->qstart.alloc((size_t)(h->ncells + 1) * 4));
   HIPCHK(h, h->bsum.alloc((size_t)2 * (nbs + 1) * 4));
   HIPCHK(h, hipMemsetAsync(h->counts.p, 0, (size_t)h->ncells * 4, s));
+  // (the scratch of the no-alloc entry point has no room to spare for them)
+  h->buckets = !t_arena && bucket_sort(h->N, h->ncells);
+  if (h->buckets && (h->bucket.alloc((size_t)h->ncells * CELL_CAP * 4) != hipSuccess ||
+                     h->over.alloc((size_t)h->N * 8) != hipSuccess || h->sortn.alloc(8) != hipSuccess)) {
+    (void)hipGetLastError();
+    h->buckets = false;  // no memory for them: sorted without
+  }
+  if (h->buckets) HIPCHK(h, hipMemsetAsync(h->sortn.p, 0, 8, s));
   HIPCHK(h, hipMemsetAsync(h->qcounts.p, 0, (size_t)h->ncells * 4, s));
 
   // half-complex mesh

@@ -204,8 +204,13 @@ struct CellView {
                      // by the permute; null when nothing reads it (no bonds)
   int* slot_a;       // [N] index in the unsorted array of each original bead
                      // index, written by the binning; null without images
+  uint32_t* bucket;  // [Ncells][CELL_CAP] beads of each cell as the binning met
+                     // them, 2 index + (charged); null: scattered after the scan
+  uint2* over;       // [N] (cell, bucket entry) of the beads that found their bucket full
+  int* sortn;        // blocks of the bucket sort that have read the counts; entries of over
   int ncells;
 };
+constexpr int CELL_CAP = 16;  // beads of a cell that its bucket holds
 
 // Global cell of a position: x-major, then y, then z within a replica, the z
 // cells of every other column (odd x nc[1] + y) counted downwards.  The order
@@ -245,6 +250,28 @@ __device__ inline int run_atomic_add(int* counts, int key, bool active) {
   return old + (lane - start);
 }
 
+// Count bead s in cell cid (and, if charged, among the charged), and put it
+// into the cell's bucket while that has room.  Every lane of the wavefront
+// must call it.
+__device__ inline void count_bead(const CellView& c, int cid, uint32_t prm, int s, bool active) {
+  const bool charged = param_z(prm) != 0;
+  const int at = run_atomic_add(c.counts, cid, active);
+  (void)run_atomic_add(c.qcounts, cid, active && charged);
+  if (c.bucket) {
+    const uint32_t entry = (uint32_t)s << 1 | (charged ? 1u : 0u);
+    if (active && at < CELL_CAP) c.bucket[(size_t)cid * CELL_CAP + at] = entry;
+    const bool full = active && at >= CELL_CAP;
+    const unsigned long long m = __ballot(full);
+    if (m != 0ull) {
+      const int first = __ffsll((long long)m) - 1, lane = threadIdx.x & 63;
+      int base = 0;
+      if (lane == first) base = atomicAdd(&c.sortn[1], __popcll(m));
+      base = __shfl(base, first, 64);
+      if (full) c.over[base + __popcll(m & ((1ull << lane) - 1ull))] = make_uint2((uint32_t)cid, entry);
+    }
+  }
+}
+
 // Record bead s's cell and count it (and, if charged, among the charged).
 // Every lane of the wavefront must call it (inactive lanes: active false).
 __device__ inline void bin_bead(const CellView& c, const RepDesc& R, uint32_t ux, uint32_t uy, uint32_t uz,
@@ -252,8 +279,7 @@ __device__ inline void bin_bead(const CellView& c, const RepDesc& R, uint32_t ux
   const int cid = active ? cell_of(R, ux, uy, uz) : 0;
   if (active) c.cell[s] = cid;
   if (active && c.slot_a) c.slot_a[id] = s;
-  (void)run_atomic_add(c.counts, cid, active);
-  (void)run_atomic_add(c.qcounts, cid, active && param_z(prm) != 0);
+  count_bead(c, cid, prm, s, active);
 }
 
 // Execution span of a launch, for the stage timers (null pointer: off):
@@ -343,6 +369,7 @@ void launch_fill_i64(hipStream_t s, long long* p, long long v, long long n);
 void launch_bin(hipStream_t s, StateView A, const RepDesc* rep, CellView c, long long* F, int N);
 // A, binned, into cell order in B, with the packed records and the charged
 // beads' copies.
+bool bucket_sort(int N, int ncells);  // whether the sort of N beads takes buckets
 void launch_sort(hipStream_t s, StateView A, StateView B, uint4* bpk, CellView c, ChargedView q, int N);
 
 // pair.hip

@@ -155,8 +155,7 @@ __global__ __launch_bounds__(BEAD_THREADS) void k_int_between(IntLaunch a, State
     if (c.slot_a) c.slot_a[id] = s;
   }
   // the binning's counts, one atomic per run of equal cells in the wavefront
-  (void)run_atomic_add(c.counts, cid, active);
-  (void)run_atomic_add(c.qcounts, cid, active && param_z(prm) != 0);
+  count_bead(c, cid, prm, s, active);
   wave_stamp(a.stamps, 1);
 }
 

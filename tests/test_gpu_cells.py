@@ -53,9 +53,11 @@ def test_cells_against_oracle(case, n, direct):
 
 # cells of the grid (rc = 1, one cell per cutoff across, two along z): the
 # scan's blocks of 4,096 cells and the cells beside them, and both sides of
-# 131,072, where the one-launch scan ends; more beads than the one-block sort
+# 24,576, where the bucket sort ends, and of 131,072, where the one-launch scan
+# does; more beads than the one-block sort
 # takes.  FP64, TOL as above.
-GRIDS = {4095: (15, 13, 21), 4096: (16, 16, 16), 4100: (10, 10, 41), 8192: (16, 16, 32),
+GRIDS = {4095: (15, 13, 21), 4096: (16, 16, 16), 4100: (10, 10, 41), 8192: (16, 16, 32), 24576: (32, 32, 24),
+         25600: (32, 32, 25),
          131040: (63, 65, 32), 131072: (64, 64, 32), 133120: (65, 64, 32)}
 
 
