@@ -333,6 +333,7 @@ CellView cview(gcme_handle h) {
   // (images change cells after the binning)
   c.bucket = h->buckets && h->nimages == 0 ? h->bucket.as<uint32_t>() : nullptr;
   c.over = h->over.as<uint2>();
+  c.nover = h->N;
   c.sortn = h->sortn.as<int>();
   c.ncells = h->ncells;
   return c;

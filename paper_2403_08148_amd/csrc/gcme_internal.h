@@ -207,6 +207,7 @@ struct CellView {
   uint32_t* bucket;  // [Ncells][CELL_CAP] beads of each cell as the binning met
                      // them, 2 index + (charged); null: scattered after the scan
   uint2* over;       // [N] (cell, bucket entry) of the beads that found their bucket full
+  int nover;         // room in over
   int* sortn;        // blocks of the bucket sort that have read the counts; entries of over
   int ncells;
 };
@@ -267,7 +268,9 @@ __device__ inline void count_bead(const CellView& c, int cid, uint32_t prm, int 
       int base = 0;
       if (lane == first) base = atomicAdd(&c.sortn[1], __popcll(m));
       base = __shfl(base, first, 64);
-      if (full) c.over[base + __popcll(m & ((1ull << lane) - 1ull))] = make_uint2((uint32_t)cid, entry);
+      const int at_over = base + __popcll(m & ((1ull << lane) - 1ull));
+      // (consistent counts list every bead once at most)
+      if (full && (unsigned)at_over < (unsigned)c.nover) c.over[at_over] = make_uint2((uint32_t)cid, entry);
     }
   }
 }
