@@ -771,26 +771,28 @@ static void launch_scan(hipStream_t s, CellView c) {
   hipLaunchKernelGGL(k_scan_apply<false>, dim3(nb), dim3(SCAN_THREADS), 0, s, c, nb);
 }
 
-bool small_sort(int N, int ncells) { return N <= SMALL_SORT_BEADS && ncells <= SMALL_SORT_CELLS; }
-
 // Buckets pay while the counts are few enough to be summed by every block and
 // a cell's bucket (64 B) holds its beads: of up to seven beads a cell on
-// average, one cell in 3,000 of an ideal gas has more than CELL_CAP.
+// average, one cell in 3,000 of an ideal gas has more than CELL_CAP.  Up to
+// 1,024 beads the one-block sort, which fetches one bead a thread, is as
+// short (700 beads 8.8 us against 8.9, 1,100 10.7 against 9.1, 1,536 13.0
+// against 9.3, 4,000 25.5 against 9.5: the step 52 -> 47); above, it serves
+// where there are no buckets.
 bool bucket_sort(int N, int ncells) {
-  return !small_sort(N, ncells) && ncells <= BUCKET_SORT_CELLS && N <= 7LL * ncells;
+  return N > SMALL_SORT_THREADS && ncells <= BUCKET_SORT_CELLS && N <= 7LL * ncells;
 }
 
 void launch_sort(hipStream_t s, StateView A, StateView B, uint4* bpk, CellView c, ChargedView q, int N) {
-  if (small_sort(N, c.ncells)) {
-    const size_t sh = ((size_t)c.ncells + N) * 4;
-    if (sh > 65536) (void)hipFuncSetAttribute((const void*)k_sort_small, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-    hipLaunchKernelGGL(k_sort_small, dim3(1), dim3(SMALL_SORT_THREADS), sh, s, A, B, bpk, c, q, N);
-    return;
-  }
   if (c.bucket) {
     // about a block per CU, of whole groups of 64 cells
     const int per = std::max(64, ((c.ncells + 255) / 256 + 63) & ~63);
     hipLaunchKernelGGL(k_sort_buckets, dim3(nblk(c.ncells, per)), dim3(BUCKET_SORT_THREADS), 0, s, A, B, bpk, c, q, N, per);
+    return;
+  }
+  if (N <= SMALL_SORT_BEADS && c.ncells <= SMALL_SORT_CELLS) {
+    const size_t sh = ((size_t)c.ncells + N) * 4;
+    if (sh > 65536) (void)hipFuncSetAttribute((const void*)k_sort_small, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+    hipLaunchKernelGGL(k_sort_small, dim3(1), dim3(SMALL_SORT_THREADS), sh, s, A, B, bpk, c, q, N);
     return;
   }
   launch_scan(s, c);

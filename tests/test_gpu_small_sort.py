@@ -66,7 +66,7 @@ def test_small_sort_replicas_and_crowded_cells():
 # so the forces are the same bits.  Block edges (64 cells), cells that their
 # buckets do not hold (a dense corner: up to hundreds in a cell), an empty
 # part of the box.
-@pytest.mark.parametrize("n,box,dense", [(4097, 12.0, 0.0), (9001, 15.4, 0.0), (5003, 14.0, 0.05), (4500, 20.0, 0.15),
+@pytest.mark.parametrize("n,box,dense", [(1025, 7.5, 0.0), (1031, 9.0, 0.5), (4097, 12.0, 0.0), (9001, 15.4, 0.0), (5003, 14.0, 0.05), (4500, 20.0, 0.15),
                                          (12289, 30.0, 0.01),
                                          (9000, 18.0, 0.6)])
 @pytest.mark.parametrize("precision", ["mixed", "fp64"])
