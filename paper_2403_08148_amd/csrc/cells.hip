@@ -452,12 +452,12 @@ __global__ __launch_bounds__(SMALL_SORT_THREADS) void k_sort_small(StateView A, 
 // cells: it adds up the counts of the cells before them itself (as
 // k_scan_self), scans its own, and moves their beads: 16 lanes, a DPP row,
 // hold the entries of a cell, whose ranks (beads of the cell with a smaller
-// previous index) are 15 row rotations.  The counts are cleared for the next
-// binning by the last block to have read them.  The beads of a cell of more
-// than CELL_CAP are ranked in LDS, from its bucket and the list of those that
-// found one full; a block with more than BUCKET_LIST of them lets one
-// wavefront meet them in order by going through all N (neither in a fluid of
-// some three beads a cell).
+// previous index) are 15 row rotations.  The counts and the length of the list
+// below are cleared for the next binning by the last block to have read them.
+// The beads of a cell of more than CELL_CAP are ranked in LDS, from its bucket
+// and the list of those that found one full; a block with more than BUCKET_LIST
+// of them lets one wavefront meet them in order by going through all N (neither
+// in a fluid of some three beads a cell).
 // It is bound by latency: the load of the counts, a block scan, then the loads
 // and stores of a bead.  Against scan, scatter and permute, the whole sort and
 // its gaps: 4,099 beads 13.0 -> 10.0 us, 32,768 15.5 -> 13.0 (ten steps 787 ->
@@ -511,11 +511,14 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_sort_buckets(StateView 
   __shared__ int s_own[2][NW], s_off[2][NW];
   __shared__ int s_cnt[BUCKET_PER_MAX], s_start[BUCKET_PER_MAX], s_qstart[BUCKET_PER_MAX];
   __shared__ uint2 s_list[BUCKET_LIST];
-  __shared__ int s_over, s_last, s_nlist;
+  __shared__ int s_over, s_last, s_nlist, s_no;
   const int n = c.ncells, c0 = blockIdx.x * per;
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
   if (c.step && blockIdx.x == 0 && t == 0) *c.step += 1ULL;
-  if (t == 0) s_over = s_nlist = 0;
+  if (t == 0) {
+    s_over = s_nlist = 0;
+    s_no = min(c.sortn[1], N);  // entries of over: read before the ticket, like the counts
+  }
   // 1. the starts of this block's cells (c0 is a multiple of 64)
   const bool mine = t < per && c0 + t < n;
   const int v0 = mine ? c.counts[c0 + t] : 0, v1 = mine ? c.qcounts[c0 + t] : 0;
@@ -553,7 +556,9 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_sort_buckets(StateView 
     s_off[0][wid] = o0;
     s_off[1][wid] = o1;
   }
-  __syncthreads();  // (every thread's loads of the counts have returned)
+  // every load of what the last block clears has returned: the ticket says so,
+  // and nothing of it may be read after
+  __syncthreads();
   int tick = 0;
   if (t == NT - 64) tick = atomicAdd(&c.sortn[0], 1);
   int r0 = i0 - v0, r1 = i1 - v1;
@@ -595,8 +600,7 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_sort_buckets(StateView 
     };
     for (int g = t >> 4; g < per; g += NT / 16)
       if (s_cnt[g] > CELL_CAP) push((uint32_t)g, c.bucket[(size_t)(c0 + g) * CELL_CAP + (t & 15)]);
-    const int no = min(c.sortn[1], N);
-    for (int i = t; i < no; i += NT) {
+    for (int i = t; i < s_no; i += NT) {
       const uint2 e = c.over[i];
       if (e.x - (uint32_t)c0 < (uint32_t)per) push(e.x - (uint32_t)c0, e.y);
     }
@@ -644,7 +648,7 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_sort_buckets(StateView 
       }
     }
   }
-  // 4. the counts, when every block has read them
+  // 4. the counts and the list's length, when every block has read them
   if (t == NT - 64) s_last = tick == (int)gridDim.x - 1;
   __syncthreads();
   if (s_last) {

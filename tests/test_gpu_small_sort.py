@@ -82,3 +82,50 @@ def test_bucket_sort_matches_scatter(n, box, dense, precision):
     print(f"case bucket sort N={n} box={box} dense={dense} {precision}", flush=True)
     for a, b in zip(_noalloc(w, precision), _context(w, precision)):
         np.testing.assert_array_equal(a, b)
+
+
+# Crowded cells (more than their buckets hold) through many sorts of one
+# context, with light and empty blocks beside the heavy ones: the beads that a
+# bucket has no room for are listed, and the list's length is cleared by the
+# block that finishes its counts last, whatever the others still have to do.
+# Each state, every position and velocity, against the same replica in a
+# context whose second replica's grid is beyond the buckets' limit (scan,
+# scatter and permute), bit for bit: forces are integer sums.
+def crowded(n, box, dense, where):
+    w = W.small_bulk(N=n, seed=14, box=(box, 1.02 * box, 0.97 * box), rc=2.3, grid=(36, 36, 36))
+    k = int(dense * n)
+    pos = w.pos.copy()
+    pos[:k] = where * box + 0.9 * np.random.default_rng(15).random((k, 3))
+    w.pos = W.lattice_positions(pos / np.asarray(w.box), w.box)
+    return w
+
+
+@pytest.mark.parametrize("n,box,dense,where", [(4099, 20.0, 0.15, 0.11), (4099, 20.0, 0.15, 0.82), (9001, 26.0, 0.3, 0.4),
+                                               (2050, 25.0, 0.05, 0.02), (20000, 12.0, 0.0, 0.0)])
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+def test_bucket_sort_crowded_cells_over_steps(n, box, dense, where, precision):
+    import dataclasses
+    from paper_2403_08148_amd import params_from_workload
+    w = crowded(n, box, dense, where)
+    far = W.small_bulk(N=300, seed=16, box=(41.0, 40.0, 42.0), rc=2.3, grid=(36, 36, 36))
+    print(f"case crowded steps N={n} box={box} dense={dense} {precision}", flush=True)
+    engs = []
+    for ws in ([w], [w, far]):
+        eng = make_engine(ws, precision, tuning=dict(beads_per_cluster=4, charges_per_cluster=2))
+        for r, x in enumerate(ws):  # (short steps: the crowd stays one)
+            eng.set_params(dataclasses.replace(params_from_workload(x), dt=1e-5), replica=r)
+        engs.append(eng)
+    for k in (0, 1, 1, 9, 30):
+        got = []
+        for eng in engs:
+            if k:
+                eng.step(k)
+                pos, vel, _ = eng.get_state()
+                got.append((pos[:, :n], vel[:, :n]))
+            else:
+                got.append((eng.forces_energy(energy=False, virial=False)["force"][:, :n],))
+            eng.sync()
+        for a, b in zip(*got):
+            np.testing.assert_array_equal(a.cpu().numpy(), b.cpu().numpy())
+    for eng in engs:
+        eng.close()
