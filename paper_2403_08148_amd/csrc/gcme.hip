@@ -261,7 +261,11 @@ struct gcme_ctx {
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
     if (own_stream && stream) (void)hipStreamDestroy(stream);
   }
+  // (waits for the context's stream first: a graph must not be destroyed while
+  // a launch of it may still run)
   void drop_graphs() {
+    if (!g_mid && !g_midn && !g_last && !g_obs) return;
+    (void)hipStreamSynchronize(stream);
     if (g_mid) (void)hipGraphExecDestroy(g_mid);
     if (g_midn) (void)hipGraphExecDestroy(g_midn);
     if (g_last) (void)hipGraphExecDestroy(g_last);
