@@ -1382,13 +1382,17 @@ void enqueue_sort(gcme_handle h, hipStream_t s, SortOf of) {
 }
 
 // Evaluations launched directly (not from a graph) run their three parts in
-// sequence on the context's stream up to this many beads: the fork and the
-// joins are seven event calls of the host, 70 us, where all the launches of a
-// small evaluation take 20.  Passes in sequence against three streams, in us:
-// 300 beads 124 / 158, 4,000 134 / 159 (FP64 125 / 149), 8,000 150 / 167;
-// waited for one by one 157 / 165, 171 / 161 (191 / 173), 184 / 188; from
-// 16,000 beads on a single evaluation is longer in sequence (228 / 191).
-constexpr int ONE_STREAM_BEADS = 4096;
+// sequence on the context's stream up to this many beads.  That saves the
+// host the fork and the join (four event calls), and costs the overlap of the
+// mesh chain with the pairs: a pass among others, bound by the host, gains at
+// any small size, one that is waited for only where the parts are short.  In
+// us, on the default two streams / in sequence (medians on three machines):
+// waited for, 300 beads 143 / 137, 500 143 / 138, 800 137 / 144, 1,200 148 /
+// 161, 1,536 143 / 165, 4,000 147 / 147, in FP64 300 148 / 142, 600 149 / 146,
+// 1,000 149 / 153, 2,000 149 / 174, 4,000 150 / 159; among others 300 beads
+// 132 / 105, 1,536 127 / 108, 4,000 128 / 114.  The line is where neither form
+// loses.
+constexpr int ONE_STREAM_BEADS = 512;
 
 // Forces (and partial sums if ev) on the sorted copy B; F must be cleared.
 // The excluded-volume kernel, the charged real-space kernel and the mesh
