@@ -454,20 +454,28 @@ __global__ __launch_bounds__(SMALL_SORT_THREADS) void k_sort_small(StateView A, 
 // hold the entries of a cell, whose ranks (beads of the cell with a smaller
 // previous index) are 15 row rotations.  The counts and the length of the list
 // below are cleared for the next binning by the last block to have read them.
-// The beads of a cell of more than CELL_CAP are ranked in LDS, from its bucket
-// and the list of those that found one full; a block with more than BUCKET_LIST
-// of them lets one wavefront meet them in order by going through all N (neither
-// in a fluid of some three beads a cell).
+// The beads of a cell of more than CELL_CAP are brought together in LDS, from
+// its bucket and the list of those that found one full, and ranked among
+// themselves; in a block with more than BUCKET_LIST of them, each wavefront
+// meets those of its own cells in order by going through all N (neither in a
+// fluid of some three beads a cell).
 // It is bound by latency: the load of the counts, a block scan, then the loads
 // and stores of a bead.  Against scan, scatter and permute, the whole sort and
 // its gaps: 4,099 beads 13.0 -> 10.0 us, 32,768 15.5 -> 13.0 (ten steps 787 ->
 // 746 us); steps of 8,000 beads 56 -> 51, 16,384 61 -> 56, 50,000 (18,000
 // cells) 84.6 -> 82, and no gain at 80,000 (29,000 cells) and above, since
-// every block reads all counts before its own.
+// every block reads all counts before its own.  Crowded systems of 20,000 cells,
+// steps with scan, scatter and permute and with this: a dense column of 7,000
+// beads in cells of 30 172 and 172 us (355 where each listed bead was compared
+// with all the block's, and 2,048 had room), a spot of cells of 380 beads 195
+// and 167 (232), a droplet 155 and 155 (165).
 constexpr int BUCKET_SORT_THREADS = 1024;
 constexpr int BUCKET_SORT_CELLS = 24576;
-constexpr int BUCKET_LIST = 2048;
-constexpr int BUCKET_PER_MAX = 1024;
+constexpr int BUCKET_LIST = 8192;
+constexpr int BUCKET_PER_MAX = 128;  // cells of a block
+// about a block per CU, of whole groups of 64 cells
+constexpr int bucket_per(int ncells) { return std::max(64, ((ncells + 255) / 256 + 63) & ~63); }
+static_assert(bucket_per(BUCKET_SORT_CELLS) <= BUCKET_PER_MAX && BUCKET_PER_MAX <= BUCKET_SORT_THREADS, "a thread per cell");
 static_assert(CELL_CAP == 16, "a cell's bucket is one DPP row");
 
 template <int R>
@@ -510,13 +518,17 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_sort_buckets(StateView 
   constexpr int NT = BUCKET_SORT_THREADS, NW = NT / 64, U = 4;
   __shared__ int s_own[2][NW], s_off[2][NW];
   __shared__ int s_cnt[BUCKET_PER_MAX], s_start[BUCKET_PER_MAX], s_qstart[BUCKET_PER_MAX];
-  __shared__ uint2 s_list[BUCKET_LIST];
-  __shared__ int s_over, s_last, s_nlist, s_no;
+  // the crowded cells' beads, cell by cell (s_seg: where a cell's begin, s_fill:
+  // how many are there), and of each the cell
+  __shared__ __align__(16) uint32_t s_key[BUCKET_LIST];
+  __shared__ uint16_t s_cell[BUCKET_LIST];
+  __shared__ int s_seg[BUCKET_PER_MAX], s_fill[BUCKET_PER_MAX];
+  __shared__ int s_last, s_nlist, s_no;
   const int n = c.ncells, c0 = blockIdx.x * per;
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
   if (c.step && blockIdx.x == 0 && t == 0) *c.step += 1ULL;
   if (t == 0) {
-    s_over = s_nlist = 0;
+    s_nlist = 0;
     s_no = min(c.sortn[1], N);  // entries of over: read before the ticket, like the counts
   }
   // 1. the starts of this block's cells (c0 is a multiple of 64)
@@ -579,7 +591,15 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_sort_buckets(StateView 
         c.qstart[n] = r1 + v1;
       }
     }
-    if (v0 > CELL_CAP) s_over = 1;
+    s_fill[t] = 0;
+    if (v0 > CELL_CAP) {
+      const int room = (v0 + 3) & ~3;
+      const int at = s_seg[t] = atomicAdd(&s_nlist, room);
+      for (int k = at + v0; k < min(at + room, BUCKET_LIST); ++k) {  // (no bead's key: after all)
+        s_key[k] = 0xffffffffu;
+        s_cell[k] = 0xffffu;
+      }
+    }
   }
   __syncthreads();
   // 2. the beads of the cells that their buckets hold
@@ -593,33 +613,38 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_sort_buckets(StateView 
     if (on) move_bead(A, B, bpk, c, q, N, (int)(key >> 1), s_start[g] + rank, s_qstart[g] + qrank);
   }
   // 3. the others
-  if (s_over) {
-    auto push = [&](uint32_t g, uint32_t key) {
-      const int at = atomicAdd(&s_nlist, 1);
-      if (at < BUCKET_LIST) s_list[at] = make_uint2(g, key);
+  const int nl = s_nlist;
+  if (nl > 0 && nl <= BUCKET_LIST) {
+    auto put = [&](int g, uint32_t key) {
+      const int at = atomicAdd(&s_fill[g], 1);
+      if (at < s_cnt[g]) {  // (as for consistent counts)
+        s_key[s_seg[g] + at] = key;
+        s_cell[s_seg[g] + at] = (uint16_t)g;
+      }
     };
     for (int g = t >> 4; g < per; g += NT / 16)
-      if (s_cnt[g] > CELL_CAP) push((uint32_t)g, c.bucket[(size_t)(c0 + g) * CELL_CAP + (t & 15)]);
+      if (s_cnt[g] > CELL_CAP) put(g, c.bucket[(size_t)(c0 + g) * CELL_CAP + (t & 15)]);
     for (int i = t; i < s_no; i += NT) {
       const uint2 e = c.over[i];
-      if (e.x - (uint32_t)c0 < (uint32_t)per) push(e.x - (uint32_t)c0, e.y);
+      const uint32_t g = e.x - (uint32_t)c0;
+      if (g < (uint32_t)per && s_cnt[g] > CELL_CAP) put((int)g, e.y);
     }
     __syncthreads();
-    const int nl = s_nlist;
-    if (nl <= BUCKET_LIST)
-      for (int i = t; i < nl; i += NT) {
-        const uint2 e = s_list[i];
-        int rank = 0, qrank = 0;
-        for (int k = 0; k < nl; ++k) {
-          const uint2 o = s_list[k];
-          const bool before = o.x == e.x && o.y < e.y;
-          rank += before;
-          qrank += before && (o.y & 1u);
-        }
-        move_bead(A, B, bpk, c, q, N, (int)(e.y >> 1), s_start[e.x] + rank, s_qstart[e.x] + qrank);
+    for (int i = t; i < nl; i += NT) {
+      const uint32_t key = s_key[i], g = s_cell[i];
+      if (g >= (uint32_t)per || s_cnt[g] <= CELL_CAP) continue;
+      const int k1 = s_seg[g] + s_cnt[g];
+      int rank = 0, qrank = 0;
+      for (int k = s_seg[g]; k < k1; k += 4) {
+        const uint4 o = *reinterpret_cast<const uint4*>(s_key + k);
+        rank += (o.x < key) + (o.y < key) + (o.z < key) + (o.w < key);
+        qrank += (o.x < key && (o.x & 1u)) + (o.y < key && (o.y & 1u)) + (o.z < key && (o.z & 1u)) +
+                 (o.w < key && (o.w & 1u));
       }
-  }
-  if (s_over && s_nlist > BUCKET_LIST && wid == 0) {
+      move_bead(A, B, bpk, c, q, N, (int)(key >> 1), s_start[g] + rank, s_qstart[g] + qrank);
+    }
+  } else if (nl > BUCKET_LIST) {
+    // each wavefront its own cells, whose s_start count up as it meets beads
     for (int b0 = 0; b0 < N; b0 += 64 * U) {
       int cid[U];
 #pragma unroll
@@ -627,7 +652,7 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_sort_buckets(StateView 
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int s = b0 + 64 * u + lane, g = cid[u];
-        const bool m = (unsigned)g < (unsigned)per && s_cnt[g] > CELL_CAP;
+        const bool m = (unsigned)g < (unsigned)per && (g & (NW - 1)) == wid && s_cnt[g] > CELL_CAP;
         unsigned long long left = __ballot(m);
         while (left) {
           const int gg = __builtin_amdgcn_readlane(g, __ffsll((long long)left) - 1);
@@ -788,8 +813,7 @@ bool bucket_sort(int N, int ncells) {
 
 void launch_sort(hipStream_t s, StateView A, StateView B, uint4* bpk, CellView c, ChargedView q, int N) {
   if (c.bucket) {
-    // about a block per CU, of whole groups of 64 cells
-    const int per = std::max(64, ((c.ncells + 255) / 256 + 63) & ~63);
+    const int per = bucket_per(c.ncells);
     hipLaunchKernelGGL(k_sort_buckets, dim3(nblk(c.ncells, per)), dim3(BUCKET_SORT_THREADS), 0, s, A, B, bpk, c, q, N, per);
     return;
   }

@@ -91,22 +91,26 @@ def test_bucket_sort_matches_scatter(n, box, dense, precision):
 # Each state, every position and velocity, against the same replica in a
 # context whose second replica's grid is beyond the buckets' limit (scan,
 # scatter and permute), bit for bit: forces are integer sums.
-def crowded(n, box, dense, where):
+def crowded(n, box, dense, where, edge):
     w = W.small_bulk(N=n, seed=14, box=(box, 1.02 * box, 0.97 * box), rc=2.3, grid=(36, 36, 36))
     k = int(dense * n)
     pos = w.pos.copy()
-    pos[:k] = where * box + 0.9 * np.random.default_rng(15).random((k, 3))
+    pos[:k] = where * box + edge * np.random.default_rng(15).random((k, 3))
     w.pos = W.lattice_positions(pos / np.asarray(w.box), w.box)
     return w
 
 
-@pytest.mark.parametrize("n,box,dense,where", [(4099, 20.0, 0.15, 0.11), (4099, 20.0, 0.15, 0.82), (9001, 26.0, 0.3, 0.4),
-                                               (2050, 25.0, 0.05, 0.02), (20000, 12.0, 0.0, 0.0)])
+@pytest.mark.parametrize("n,box,dense,where,edge", [
+    (4099, 20.0, 0.15, 0.11, 0.9), (4099, 20.0, 0.15, 0.82, 0.9), (9001, 22.0, 0.3, 0.4, 0.9), (2050, 22.0, 0.05, 0.02, 0.9),
+    (20000, 12.0, 0.0, 0.0, 0.0),  # the rule's limit of seven beads a cell
+    (6000, 20.0, 0.9, 0.3, 3.0),   # crowded cells of every count modulo four, in many blocks
+    (20000, 20.0, 0.5, 0.1, 0.35),  # more in one block than it takes into LDS
+])
 @pytest.mark.parametrize("precision", ["mixed", "fp64"])
-def test_bucket_sort_crowded_cells_over_steps(n, box, dense, where, precision):
+def test_bucket_sort_crowded_cells_over_steps(n, box, dense, where, edge, precision):
     import dataclasses
     from paper_2403_08148_amd import params_from_workload
-    w = crowded(n, box, dense, where)
+    w = crowded(n, box, dense, where, edge)
     far = W.small_bulk(N=300, seed=16, box=(41.0, 40.0, 42.0), rc=2.3, grid=(36, 36, 36))
     print(f"case crowded steps N={n} box={box} dense={dense} {precision}", flush=True)
     engs = []
