@@ -662,12 +662,12 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_sort_buckets(StateView 
           const unsigned long long below = (1ull << lane) - 1ull;
           const int base = s_start[gg], qbase = s_qstart[gg];
           if (take) move_bead(A, B, bpk, c, q, N, s, base + __popcll(mm & below), qbase + __popcll(mq & below));
-          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (every lane has read them)
           if (lane == 0) {
             s_start[gg] = base + __popcll(mm);
             s_qstart[gg] = qbase + __popcll(mq);
           }
-          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
           left &= ~mm;
         }
       }
