@@ -1,8 +1,9 @@
-"""The sort of small systems in one block (up to 4,096 beads, four per
-thread) and the first size past it, against the FP64 oracle and, for the
-order it leaves the beads in, a run of steps against single steps (bit for
-bit).  Sizes at the edges of its threads' shares; crowded cells (one cell per
-axis), several replicas in one context, and a bead count below one wavefront.
+"""The sort of small systems (one block up to 1,024 beads, and up to 4,096
+where no buckets are taken; from buckets above) against the FP64 oracle and,
+for the order it leaves the beads in, a run of steps against single steps (bit
+for bit).  Sizes at the edges of its threads' shares; crowded cells (one cell
+per axis), several replicas in one context, and a bead count below one
+wavefront.
 """
 import numpy as np
 import pytest
@@ -133,3 +134,46 @@ def test_bucket_sort_crowded_cells_over_steps(n, box, dense, where, edge, precis
             np.testing.assert_array_equal(a.cpu().numpy(), b.cpu().numpy())
     for eng in engs:
         eng.close()
+
+
+# The one-block sort at every share of its threads, where the context takes no
+# buckets: with image charges, over steps, against the same replica beside one
+# whose grid is beyond the one-block sort (scan, scatter and permute), and in
+# the no-alloc entry point, against buckets; bit for bit as above.
+@pytest.mark.parametrize("n", [1023, 1025, 2049, 3072, 3073, 4095, 4096])
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+def test_one_block_sort_without_buckets(n, precision):
+    from paper_2403_08148_amd import GCMe, params_from_workload
+    from tests.test_zz_no_alloc import _context, _noalloc
+    box = box_of(n)
+    w = W.small_bulk(N=n, seed=n, box=box, rc=2.0, grid=(24, 24, 24))
+    far = W.small_bulk(N=300, seed=16, box=(41.0, 40.0, 42.0), rc=2.0, grid=(24, 24, 24))
+    print(f"case one-block sort N={n} {precision}", flush=True)
+    for a, b in zip(_noalloc(w, precision), _context(w, precision)):
+        np.testing.assert_array_equal(a, b)
+    # a third type that does not move: images of the first positive beads
+    def with_image_type(x):
+        A = np.full((3, 3), 25.0)
+        A[:2, :2] = x.A
+        return params_from_workload(x, A=A, sigma=np.append(x.sigma, 0.5), a=np.append(x.a, 0.5),
+                                    mass=np.array([1.0, 1.0, np.inf]))
+    k = n // 12
+    src, img = np.nonzero(w.z == 1)[0][:k], np.nonzero(w.z == -1)[0][:k]
+    w.type[img] = 2
+    got = []
+    for ws in ([w], [w, far]):
+        eng = GCMe([x.N for x in ws], precision=precision, seed=1)
+        for r, x in enumerate(ws):
+            eng.set_params(with_image_type(x), replica=r)
+        eng.set_tuning(beads_per_cluster=4, charges_per_cluster=2)
+        eng.set_images(np.stack([img, src], 1))
+        eng.set_state(*(np.concatenate([getattr(x, f) for x in ws]) for f in ("pos", "type", "z", "vel")))
+        out = [eng.forces_energy(energy=False, virial=False)["force"][:, :n]]
+        for steps in (1, 9):
+            eng.step(steps)
+            out += [t[:, :n] for t in eng.get_state()[:2]]
+        eng.sync()
+        got.append([t.cpu().numpy() for t in out])
+        eng.close()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
