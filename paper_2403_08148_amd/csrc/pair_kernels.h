@@ -215,7 +215,10 @@ __device__ inline void make_box(ClusterBox& K, const uint4 me, const RepDesc& R,
     const int du = (int)(u[k] - b0);
     const int dlo = __builtin_amdgcn_readfirstlane(group_reduce<CI>(du, lower));
     const int dhi = __builtin_amdgcn_readfirstlane(group_reduce<CI>(du, upper));
-    const int mid = dlo / 2 + dhi / 2;
+    // (rounded up: dlo - mid and dhi - mid stay within 32 bits for a cluster
+    // as wide as the axis)
+    const uint32_t wid = (uint32_t)dhi - (uint32_t)dlo;
+    const int mid = (int)((uint32_t)dlo + (wid >> 1) + (wid & 1u));
     K.u0[k] = b0 + (uint32_t)mid;
     r[k] = (float)((double)(du - mid) * R.scaled[k]);
     K.lo[k] = uni((float)(dlo - mid) * R.scalef[k]);

@@ -116,3 +116,26 @@ def test_given_cluster_sizes_stand():
     np.testing.assert_array_equal(given.cpu().numpy(), ref.cpu().numpy())
     assert rel_rms(auto.cpu().numpy(), ref.cpu().numpy()) < TOL["mixed"]
     fresh.close()
+
+
+@pytest.mark.parametrize("direct", [0, 3])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+def test_cluster_across_the_whole_axis(axis, direct, precision):
+    """One cluster with beads half the axis away on either side, 2^31 and
+    2^31 - 1 units of the fixed-point lattice from its first: its bounding box
+    is the axis to the last unit."""
+    w = W.small_bulk(N=8, seed=10, box=(10.0, 10.0, 10.0), rc=2.0, charged_frac=0.5, grid=(24, 24, 24))
+    f = np.full((8, 3), 0.04)
+    f[:, (axis + 1) % 3] += np.linspace(0.0, 0.05, 8)
+    f[:, (axis + 2) % 3] += np.linspace(0.05, 0.0, 8)
+    f[:, axis] = np.array([0.0, 2.0**31, 2.0**31 - 1, 1e8, 2e8, 3e8, 2.0**31 - 2e8, 2.0**31 - 3e8]) / 2.0**32
+    f[0, (axis + 1) % 3] = f[0, (axis + 2) % 3] = 0.0  # (the first in cell order)
+    w.pos = W.lattice_positions(f, w.box)
+    ref = oracle_eval(w)
+    eng = make_engine([w], precision, tuning=dict(beads_per_cluster=8, charges_per_cluster=8, direct_pairs=direct,
+                                                  list_slack_pct=1000))
+    out = eng.forces_energy()
+    eng.sync()
+    assert rel_rms(out["force"].t().cpu().numpy(), ref["F"]) < TOL[precision]
+    eng.close()
