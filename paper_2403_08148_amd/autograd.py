@@ -36,7 +36,7 @@ def _sym_weights(engine, nt):
     so complete for every stream)."""
     kept = engine.__dict__.setdefault("_sym_weights", {})
     if nt not in kept:
-        kept[nt] = (0.5 * (1.0 + torch.eye(nt, dtype=torch.float64))).to(engine.device)
+        kept[nt] = (0.5 * (1.0 + torch.eye(nt, dtype=torch.float64, device="cpu"))).to(engine.device)
     return kept[nt]
 
 
