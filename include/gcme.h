@@ -331,7 +331,9 @@ gcme_status gcme_forces_energy_noalloc(const gcme_params* p, int32_t n_beads, in
  * its cell columns directly).  Both visit the same pairs with the same
  * cutoff test; they differ in the order of the per-bead sums.  While no
  * cluster size has been given, the list-free pairs of a small system take
- * smaller clusters than the default that gcme_get_tuning reports. */
+ * smaller clusters than the default that gcme_get_tuning reports; while no
+ * stream layout has been given, systems whose pairs take longest run in
+ * layout 0. */
 typedef struct {
     int32_t cells_per_cutoff;    /* cells of about (rc / n)^3, flat along z (1..4) */
     int32_t beads_per_cluster;   /* excluded-volume cluster size (2, 4, 8) */

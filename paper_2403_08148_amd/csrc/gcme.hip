@@ -157,6 +157,8 @@ struct gcme_ctx {
   // 84 / 104 and 106 / 111; the adsorption study's slabs 845 / 916 and 743 / 786
   // for four; N = 2,097,152 alike)
   gcme_tuning tune{3, 8, 4, 50, 3, 2, 0, 0, 0, 0, 0};
+  bool layout_given = false;          // a caller (or the autotuner) chose the stream layout
+  double partners = 0.0;              // of the plan: beads within the cutoff of one, on average
   bool ci_given[2] = {false, false};  // a caller (or the autotuner) chose the cluster sizes: beads, charges
   int ci[2] = {8, 4};                 // ... and those of the plan
   bool plan_dirty = true;
@@ -599,6 +601,23 @@ int cluster_size(gcme_handle h, bool charged) {
   return ci;
 }
 
+// The stream layout: what the tuning gives, or, where no caller has given one,
+// its default (the mesh chain on one stream, both pair kernels on a second) but
+// three branches where the pair kernels in sequence outlast the mesh chain by
+// more than the third branch costs: from 1,000 beads within a bead's cutoff on,
+// or with column clusters for the charged pairs, which take a launch more.
+// Steps in us, three branches and the default: 8,000 beads of 700, 900, 1,200
+// and 2,400 partners 87 / 81, 97 / 102, 100 / 114 and 209 / 245, 30,000 beads
+// 120 / 107, 127 / 124, 138 / 152 and 237 / 292, 100,000 beads 214 / 207, 242 /
+// 240, 265 / 291 and 517 / 577, and in FP64 (30,000) 171 / 184, 195 / 221, 239 /
+// 279 and 440 / 545; column clusters both ends at 3,000 beads of 164 partners
+// 62 / 82, in FP64 73 / 98, at 24,000 102 / 95 and 129 / 155.
+constexpr double THREE_BRANCH_PARTNERS = 1000.0;
+int stream_layout(gcme_handle h) {
+  if (h->layout_given || (h->partners < THREE_BRANCH_PARTNERS && !col_mode(h, true))) return h->tune.stream_layout;
+  return 0;
+}
+
 // Clusters of `ci` consecutive beads of each replica's sorted population
 // (all beads, or the compacted charged beads), tiled in groups of
 // pair_waves_per_block() clusters of one replica (one pair-kernel workgroup
@@ -718,6 +737,8 @@ gcme_status build_plan(gcme_handle h) {
     h->maxK[1] = std::max(h->maxK[1], p.K[1]);
     h->maxK[2] = std::max(h->maxK[2], p.K[0]);
   }
+  h->partners = 0.0;
+  for (const RepDesc& d : h->rep) h->partners += (4.0 / 3.0) * M_PI * d.rc * d.rc2 * d.n / d.V * d.n / h->N;
   h->ncells = cell_off;
   h->grid_total = goff;
   h->cgrid_total = cgoff;
@@ -1421,7 +1442,7 @@ void enqueue_forces(gcme_handle h, hipStream_t s, bool ev, bool adj, bool one_st
   // a context without auxiliary streams (the no-alloc entry point's) runs
   // the three parts in sequence on s
   static const Layout kSingle = {0, 0, 0, "gqp"};
-  const Layout& L = h->aux[0] && !one_stream ? kLayouts[h->tune.stream_layout] : kSingle;
+  const Layout& L = h->aux[0] && !one_stream ? kLayouts[stream_layout(h)] : kSingle;
   hipStream_t st3[3] = {s, h->aux[0], h->aux[1]};
   hipStream_t sg = st3[L.g], sq = st3[L.q], sp = st3[L.p];
   const bool use1 = L.g == 1 || L.q == 1 || L.p == 1, use2 = L.g == 2 || L.q == 2 || L.p == 2;
@@ -2193,9 +2214,10 @@ gcme_status gcme_set_tuning(gcme_handle h, const gcme_tuning* t) {
   }
   if (t->stream_layout >= 0) {
     if (t->stream_layout > 5) return fail(h, GCME_EINVAL, "stream_layout in 0..5");
-    if (t->stream_layout != h->tune.stream_layout) h->drop_graphs();  // no new plan needed
-    n.stream_layout = t->stream_layout;
-    h->tune.stream_layout = n.stream_layout;
+    const int was = stream_layout(h);
+    n.stream_layout = h->tune.stream_layout = t->stream_layout;
+    h->layout_given = true;
+    if (stream_layout(h) != was) h->drop_graphs();  // no new plan needed
   }
   {
     const int32_t* in[4] = {&t->mesh_tile_x, &t->mesh_tile_y, &t->gather_tile_x, &t->gather_tile_y};

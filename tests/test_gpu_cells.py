@@ -139,3 +139,27 @@ def test_cluster_across_the_whole_axis(axis, direct, precision):
     eng.sync()
     assert rel_rms(out["force"].t().cpu().numpy(), ref["F"]) < TOL[precision]
     eng.close()
+
+
+# The stream layout that is taken while none is given (three branches from 1,000
+# beads within a bead's cutoff on, or with column clusters for the charges)
+# changes no result: forces are integer sums.
+@pytest.mark.parametrize("n,box,tuning", [(4000, 6.3, {}), (4000, 6.5, {}), (3000, 10.6, dict(half_pairs=10)),
+                                          (3000, 10.6, dict(half_pairs=2))])
+def test_layouts_agree(n, box, tuning):
+    w = W.small_bulk(N=n, seed=11, box=(box, box, box), rc=2.5, grid=(24, 24, 24))
+    states = []
+    for layout in (None, 0, 2, None):
+        eng = make_engine([w], "mixed", tuning=dict(tuning) if layout is None else dict(tuning, stream_layout=layout))
+        eng.step(10)
+        if layout is None and states:  # given between two runs
+            eng.set_tuning(stream_layout=2)
+            eng.set_state(w.pos, w.type, w.z, w.vel)
+            eng.step(10)
+        pos, vel, _ = eng.get_state()
+        eng.sync()
+        states.append((pos.cpu().numpy(), vel.cpu().numpy()))
+        eng.close()
+    for s in states[1:]:
+        np.testing.assert_array_equal(s[0], states[0][0])
+        np.testing.assert_array_equal(s[1], states[0][1])
