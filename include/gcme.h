@@ -335,7 +335,8 @@ gcme_status gcme_forces_energy_noalloc(const gcme_params* p, int32_t n_beads, in
  * stream layout has been given, systems whose pairs take longest run in
  * layout 0. */
 typedef struct {
-    int32_t cells_per_cutoff;    /* cells of about (rc / n)^3, flat along z (1..4) */
+    int32_t cells_per_cutoff;    /* n = 1..4: n - 1 cells per cutoff radius along x
+                                    and y (n for n < 3), 2 n along z */
     int32_t beads_per_cluster;   /* excluded-volume cluster size (2, 4, 8) */
     int32_t charges_per_cluster; /* real-space electrostatics cluster size (2, 4, 8) */
     int32_t list_slack_pct;      /* list capacity above the density estimate, % (0..1000) */

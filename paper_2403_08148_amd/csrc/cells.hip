@@ -337,8 +337,10 @@ __global__ void k_permute(StateView A, StateView B, uint4* __restrict__ bpk, Cel
 
 // The whole sort (scan, scatter and permute) in one block, for small systems,
 // where the three launches and the gaps between them take longer than the
-// work: N = 1,536 went from 10 us in three launches, and 12 us between them,
-// to 9 us in one.  The cell counts of all beads (low half) and of the charged
+// work.  With image charges, so that no buckets serve, three launches and this:
+// 500 beads 53.4 and 47.1 us a step, 1,000 57.6 and 50.9 (in FP64 62.5 and
+// 56.7), 3,000 58.4 and 57.2, 4,096 59.6 and 59.5, where the line lies.  The
+// cell counts of all beads (low half) and of the charged
 // ones (high half) are scanned together in LDS; the scattered bead indices
 // stay there too (with a mark for the charged ones), so the ranks within a
 // cell are LDS reads.
@@ -801,8 +803,8 @@ static void launch_scan(hipStream_t s, CellView c) {
 }
 
 // Buckets pay while the counts are few enough to be summed by every block and
-// a cell's bucket (64 B) holds its beads: of up to seven beads a cell on
-// average, one cell in 3,000 of an ideal gas has more than CELL_CAP.  Up to
+// a cell's bucket (64 B) holds its beads: at seven beads a cell on average, the
+// limit, one cell in 1,000 of an ideal gas has more than CELL_CAP.  Up to
 // 1,024 beads the one-block sort, which fetches one bead a thread, is as
 // short (700 beads 8.8 us against 8.9, 1,100 10.7 against 9.1, 1,536 13.0
 // against 9.3, 4,000 25.5 against 9.5: the step 52 -> 47); above, it serves

@@ -683,11 +683,12 @@ gcme_status build_plan(gcme_handle h) {
       d.L[k] = p.box[k];
       d.scaled[k] = p.box[k] / 4294967296.0;
       d.scalef[k] = (float)d.scaled[k];
-      // Cells per cutoff radius: n = cells_per_cutoff sets the cells' volume,
-      // (rc / n)^3 or a little less; their shape is wider than high.  A
-      // cluster is consecutive beads of a column, so wide flat cells make it
-      // compact (fewer candidates, more of each within the cutoff) and halve
-      // the columns to enumerate, while fine z cells clip the runs closely.
+      // Cells per cutoff radius, n = cells_per_cutoff: n - 1 along x and y (n
+      // for n < 3) and 2 n along z, so 2, 16, 24 and 72 to rc^3 for n = 1 to
+      // 4, each wider than high.  A cluster is consecutive beads of a column,
+      // so wide flat cells make it compact (fewer candidates, more of each
+      // within the cutoff) and halve the columns to enumerate, while fine z
+      // cells clip the runs closely.
       // Excluded-volume pairs alone, in us, at (cells along x and y, z):
       // N = 32,768 (2,6) 25.9, (3,3) 26.9, (3,6) 26.8, (2,2) 28.9;
       // N = 2,097,152 (2,4) 692, (2,6) 682 with 18 us more of sorting,
