@@ -462,6 +462,7 @@ void build_tables(gcme_handle h, std::vector<GcmPar<T>>& g, std::vector<ElecPar<
 // each time: with the whole plan built again, 46 copies and the host's
 // tables, that took 1.1 ms of the 1.2 ms of a gradient over 8 replicas.)
 gcme_status upload_tables(gcme_handle h) {
+  HIPCHK(h, hipSetDevice(h->device));
   const int R = h->R;
   const size_t np = (size_t)R * MAXT * MAXT, nt = (size_t)R * MAXT, ft = h->fp64 ? 8 : 4;
   const size_t size[gcme_ctx::N_PT] = {np * ft * (sizeof(GcmPar<float>) / 4), np * ft * (sizeof(ElecPar<float>) / 4),

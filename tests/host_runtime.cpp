@@ -3,7 +3,8 @@
 // streams, events, captures and executable graphs are tracked.  Misuse (a
 // graph destroyed while a launch of it may still run, an event of an ended
 // capture waited for, a stream left unjoined by a capture, copies or fills in
-// a capture, launches out of the documented limits) is counted and printed.
+// a capture, work issued while another device is current, launches out of the
+// documented limits) is counted and printed.
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -37,7 +38,7 @@ struct {
 struct All {
   std::set<void*> streams, events, graphs, execs;
   Stream null;
-  int misuses = 0;
+  int misuses = 0, device = 0;
 };
 All& all() {
   static All* a = new All;  // (the library's static constructors come first)
@@ -60,6 +61,10 @@ T* known(std::set<void*>& s, void* p, const char* what) {
     exit(3);
   }
   return static_cast<T*>(p);
+}
+// (every context of the tests is on device 0)
+void on_device(const char* what) {
+  if (all().device != 0) misuse("%s with another device current", what);
 }
 Stream* stream_of(void* s) { return s ? known<Stream>(all().streams, s, "stream") : &all().null; }
 
@@ -93,13 +98,16 @@ int hipDeviceGetAttribute(int* v, int, int) {
   *v = 163840;
   return 0;
 }
-int hipSetDevice(int) { return 0; }
+int hipSetDevice(int d) {
+  all().device = d;
+  return 0;
+}
 int hipGetDevice(int* d) {
-  *d = 0;
+  *d = all().device;
   return 0;
 }
 int hipGetDeviceCount(int* d) {
-  *d = 1;
+  *d = 2;
   return 0;
 }
 const char* hipGetErrorString(int) { return "error"; }
@@ -111,6 +119,7 @@ int hipGetSymbolAddress(void** p, const void*) {
   return 0;
 }
 int hipMalloc(void** p, size_t n) {
+  on_device("allocation");
   *p = malloc(n);
   if (*p) memset(*p, 0xa5, n);
   return *p ? 0 : 2;
@@ -120,19 +129,23 @@ int hipFree(void* p) {
   return 0;
 }
 int hipMemcpy(void* d, const void* s, size_t n, int) {
+  on_device("copy");
   if (n) memcpy(d, s, n);
   return 0;
 }
 int hipMemcpyAsync(void* d, const void* s, size_t n, int, void* st) {
+  on_device("copy");
   if (stream_of(st)->cap) misuse("copy in a capture");
   if (n) memcpy(d, s, n);
   return 0;
 }
 int hipMemset(void* d, int v, size_t n) {
+  on_device("fill");
   memset(d, v, n);
   return 0;
 }
 int hipMemsetAsync(void* d, int v, size_t n, void* st) {
+  on_device("fill");
   if (stream_of(st)->cap) misuse("fill in a capture");
   memset(d, v, n);
   return 0;
@@ -201,6 +214,7 @@ int hipStreamWaitEvent(void* s, void* e, unsigned) {
   return 0;
 }
 int hipStreamBeginCapture(void* s, int) {
+  on_device("capture");
   Stream* t = stream_of(s);
   if (t->cap) misuse("capture in a capture");
   t->cap = new Capture{s, true, {s}, {}};
@@ -219,6 +233,7 @@ int hipStreamEndCapture(void* s, void** g) {
   return 0;
 }
 int hipGraphInstantiate(void** x, void* g, void**, char*, size_t) {
+  on_device("instantiation");
   known<char>(all().graphs, g, "graph");
   all().execs.insert(*x = new char);
   return 0;
@@ -229,6 +244,7 @@ int hipGraphDestroy(void* g) {
   return 0;
 }
 int hipGraphLaunch(void* x, void* s) {
+  on_device("graph launch");
   known<char>(all().execs, x, "executable graph");
   stream_of(s)->in_flight.insert(x);
   return 0;
@@ -242,6 +258,7 @@ int hipGraphExecDestroy(void* x) {
   return 0;
 }
 int hipLaunchKernel(const void*, dim3 g, dim3 b, void**, size_t lds, void* s) {
+  on_device("launch");
   Stream* t = stream_of(s);
   if (!g.x || !g.y || !g.z || !b.x || b.x * b.y * b.z > 1024 || lds > 163840)
     misuse("launch of %u x %u blocks of %u threads with %zu bytes of LDS", g.x, g.y, b.x, lds);

@@ -1,7 +1,7 @@
 """The library's host code against a stand-in for the HIP runtime that tracks
 streams, events, captures and graphs (host_runtime.cpp): no call may destroy
-a graph that can still be running, leave a capture unjoined or launch beyond
-the documented limits.  Kernels do nothing, so outputs are not looked at."""
+a graph that can still be running, leave a capture unjoined, work while
+another device is current or launch beyond the documented limits.  Kernels do nothing, so outputs are not looked at."""
 import os
 import re
 import shutil
@@ -70,6 +70,7 @@ def run(calls, n, fp64, rng):
     params()
     state()
     for c in calls or rng.choices(sorted(set(do) - {"autotune"}), k=25):
+        stub.hipSetDevice(1)  # (a program's own choice between two calls)
         do[c]()
     L.gcme_destroy(h)
 
